@@ -173,7 +173,7 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
   // at batch 1, 5.2-5.4 -> 4.8 ms).
   p.afrag = c->dtype == DPARA_BF16 && p.M > 64 && p.M <= 320 && H % 256 == 0;
   p.s_qkv = gemm_splits(p.afrag ? A_BF16_FRAG : amode, EPI_STORE_F32, p.M, (nq + 2 * nkv) * hd, H);
-  p.qkv_fused = c->dtype == DPARA_BF16 && hd == 128 && p.M > 1024 && p.s_qkv == 1;
+  p.qkv_fused = c->dtype == DPARA_BF16 && hd == 128 && p.M > 1024 && p.s_qkv == 1 && H % 128 == 0;
   p.s_o = gemm_splits(amode, EPI_STORE_F32, p.M, H, nq * hd);
   p.s_down = gemm_splits(amode, EPI_STORE_F32, p.M, H, c->ffn);
   const size_t M = p.M;

@@ -253,83 +253,6 @@ __global__ __launch_bounds__(64 * WMW * WNW) void gemm_pipe_kernel(GemmArgs a, i
     }
   }
 
-  if constexpr (EPI == EPI_QKV) {
-    // One 128-wide head per wave column: the row's sum of squares over the head is this
-    // lane's eight columns plus the 16 lanes sharing the row (DPP), and RoPE's rotate-half
-    // partner of column d (d +- 64) is fragment ni +- 4 of the same lane.  Same arithmetic as
-    // the q/k-norm kernel: y = x * (1 / sqrt(ss / 128 + eps)) * g, then
-    // y_d = y_d cos - y_{d+64} sin, y_{d+64} = y_{d+64} cos + y_d sin.  The bf16 results go
-    // through this wave's part of the (now free) LDS ring, [WM rows][128 + 8 columns], so that
-    // Q and K leave as 16-byte row pieces and V^T as 64 consecutive rows per store (the launch
-    // sizes the dynamic LDS for this staging: up to 139 KB against the 128 KB ring).
-    static_assert(WN == 128 && FN == 8 && WM <= 64 && DUAL == 0, "one 128-wide head per wave column");
-    constexpr int LDT = 136;  // staging row stride in bf16 (272 bytes: rows fall on different banks)
-    const QkvEpi& e = a.qkv;
-    const int slot = nt * (BN / 128) + wn;
-    const int grp = e.n_q / e.n_kv;
-    const bool live = slot < e.n_q + 2 * e.n_kv;
-    const bool isv = slot >= e.n_q + e.n_kv, isq = slot < e.n_q;
-    bf16_t* stg = (bf16_t*)smem + wave * WM * LDT;
-    __syncthreads();  // every wave is done with the ring
-    if (!live) return;  // past the last head (no barrier follows)
-    const float* gain = isq ? e.qn : e.kn;
-    const int row0 = m0 + wm * WM;  // this wave's first row
-#pragma unroll
-    for (int mi = 0; mi < FM; ++mi) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int lrow = mi * 16 + lc * 4 + r, row = row0 + lrow;
-        float v[FN];
-#pragma unroll
-        for (int ni = 0; ni < FN; ++ni) v[ni] = acc[mi][ni][r];
-        if (!isv) {
-          if (e.qk_norm) {
-            float ss = 0.f;
-#pragma unroll
-            for (int ni = 0; ni < FN; ++ni) ss += v[ni] * v[ni];
-            ss = row16_sum(ss);
-            const float rn = 1.0f / sqrtf(ss / 128.0f + e.eps);
-#pragma unroll
-            for (int ni = 0; ni < FN; ++ni) v[ni] = v[ni] * rn * gain[ni * 16 + lr];
-          }
-          const int rc = min(row, a.M - 1), b = rc / e.R;
-          const float2* cs = e.table + ((int64_t)b * (2 * e.gamma + 1) + row_pos_offset(rc - b * e.R, e.gamma)) * 64 + lr;
-#pragma unroll
-          for (int ni = 0; ni < FN / 2; ++ni) {
-            const float2 c = cs[ni * 16];
-            const float lo = v[ni], hi = v[ni + 4];
-            v[ni] = lo * c.x + -1.f * hi * c.y;
-            v[ni + 4] = hi * c.x + 1.f * lo * c.y;
-          }
-        }
-#pragma unroll
-        for (int ni = 0; ni < FN; ++ni) stg[lrow * LDT + ni * 16 + lr] = f2bf(v[ni]);
-      }
-    }
-    if (!isv) {
-      // row pieces: lane (rq, piece) stores 16 bytes = columns 8 piece .. +7 of rows rq, rq+4, ...
-      const int piece = lane & 15;
-#pragma unroll 4
-      for (int lrow = lane >> 4; lrow < WM; lrow += 4) {
-        const int row = row0 + lrow;
-        if (row >= a.M) break;
-        const int b = row / e.R, rr = row - b * e.R;
-        bf16_t* dst = isq ? (bf16_t*)e.Q + (((int64_t)(b * e.n_kv + slot / grp) * grp + slot % grp) * e.R + rr) * 128
-                          : (bf16_t*)e.Kb + ((int64_t)(b * e.n_kv + (slot - e.n_q)) * e.Rp + rr) * 128;
-        *(uint4*)(dst + piece * 8) = *(const uint4*)(stg + lrow * LDT + piece * 8);
-      }
-    } else {
-      // V^T [128][Rp]: lane = row, one store per head dimension (WM consecutive rows of a
-      // request, split where a request ends)
-      const int row = row0 + lane;
-      if (lane < WM && row < a.M) {
-        const int b = row / e.R, rr = row - b * e.R;
-        bf16_t* dst = (bf16_t*)e.Vb + (int64_t)(b * e.n_kv + (slot - e.n_q - e.n_kv)) * 128 * e.Rp + rr;
-        for (int d = 0; d < 128; ++d) dst[(int64_t)d * e.Rp] = stg[lane * LDT + d];
-      }
-    }
-    return;
-  }
   if constexpr (EPI == EPI_TOP2) {
     // One (key1, key2, third value) triple per row and 128-column tile (WPT wave columns each):
     // per lane over its columns of each row (FN of them); then the 16 lanes that share the
@@ -651,8 +574,7 @@ hipError_t run_pipe(const GemmArgs& a, hipStream_t st) {
   const int MT = (a.M + BM - 1) / BM;
   const int NT = EPI == EPI_SWIGLU ? (a.N + BN / 2 - 1) / (BN / 2) : (a.N + BN - 1) / BN;
   constexpr int ring = STAGES * ((DUAL ? 2 : 1) * BM + BN) * BKB;
-  constexpr int stage_out = EPI == EPI_QKV ? (BM / WMW) * WMW * WNW * 136 * 2 : 0;  // the QKV epilogue's staging
-  constexpr int lds = ring > stage_out ? ring : stage_out;
+  constexpr int lds = ring;
   static_assert(lds <= 163840, "LDS ring exceeds 160 KB");
   auto kern = gemm_pipe_kernel<BM, BN, WMW, WNW, STAGES, BKB, EPI, DUAL>;
   static const hipError_t attr =
@@ -665,82 +587,17 @@ hipError_t run_pipe(const GemmArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Tile choice for the bf16 projections (measured on MI355X at Qwen3-8B N/K):
-//  M <= 320 : weight streaming.  One 320-row tile covers every row, so each weight tile is
+// Tile choice for the bf16 projections of at most 320 rows (measured on MI355X at Qwen3-8B N/K):
+//  65-320   : weight streaming.  One 320-row tile covers every row, so each weight tile is
 //             read once; 8 waves (80x64 each), a 2-deep ring of 64-wide K steps (SwiGLU:
 //             320x96 tiles of 4 waves, 80 x (48 gate + 48 up) each).  The
 //             fp32-store GEMMs (QKV, O, down, append) split K so that about 256 workgroups
 //             run; their consumers add the S partial planes (gemm_splits).
-//  M <= 64 (the context append, up to gamma+1 rows per request) and 320 < M <= 1024:
-//             64x128 tiles, 3-deep ring;
-//  larger   : 256x256 tiles, 8 waves (128x64 per wave), 2-deep ring.
-// Fraction of the last round of workgroups that has work (one workgroup per CU) for
-// BM x 256 tiles: 192-row tiles are taken when they fill the rounds clearly better (the
-// Qwen3-8B O / down projections at 4624 rows: 304 tiles = 1.19 rounds with 256 rows, 400 =
-// 1.56 with 192, measured 11% faster on MI355X).
-double round_fill(int M, int N, int BM) {
-  const double w = (double)((M + BM - 1) / BM) * ((N + 255) / 256) / 256.0;
-  return w / ceil(w);
-}
-
+//  M <= 64  : (the context append, up to gamma+1 rows per request) 64x128 tiles, 3-deep ring.
+// More rows come here only when gemm_large_supported() says no (K not a multiple of 128): the
+// 64-row tiles take any shape.
 template <int EPI>
 hipError_t run_bf16(const GemmArgs& a, hipStream_t st) {
-  if (a.M > 1024) {
-    if constexpr (EPI == EPI_STORE_F32) {
-      // Fewer than 192 tiles of 256 x 256 (under three quarters of one round, e.g. the
-      // 2048-row feature fusion, 4096 columns: 128 tiles): 128 x 128 tiles at two workgroups
-      // per CU fill the chip instead.
-      if (a.splits == 1 && (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256) < 192)
-        return run_pipe<128, 128, 2, 2, 2, 128, EPI>(a, st);
-      // One weight matrix, no split-K: when the last round of BM x 256 tiles is at most 60%
-      // full, the columns of that round go to a second launch of 128 x 128 tiles (two
-      // workgroups per CU) and the first runs whole rounds only.  Measured on MI355X at
-      // Qwen3-8B batch 16 (4624 rows, 400 tiles of 192 x 256 = 1.56 rounds): O 876 -> 858,
-      // down 2404 -> 2342 us per step.
-      const bool bm192 = round_fill(a.M, a.N, 192) > round_fill(a.M, a.N, 256) + 0.1;
-      const int BMc = bm192 ? 192 : 256;
-      const int MT = (a.M + BMc - 1) / BMc, NT = (a.N + 255) / 256, T = MT * NT;
-      const int NT1 = (T / 256) * 256 / MT;  // 256-column tiles of the whole rounds
-      if (a.splits == 1 && a.seg_rows == 0 && a.n1 >= a.N && T % 256 != 0 && T % 256 <= 256 * 6 / 10 && NT1 > 0 &&
-          NT1 < NT) {
-        GemmArgs head = a, tail = a;
-        const int n0 = NT1 * 256;
-        head.N = n0;
-        tail.B0 = tail.B1 = tail.B2 = (const bf16_t*)a.B0 + (int64_t)n0 * a.K;
-        tail.n1 = tail.n2 = a.N - n0;
-        tail.C = (float*)a.C + n0;
-        tail.N = a.N - n0;
-        const hipError_t e = bm192 ? run_pipe<192, 256, 2, 4, 2, 128, EPI>(head, st)
-                                   : run_pipe<256, 256, 2, 4, 2, 128, EPI>(head, st);
-        if (e != hipSuccess) return e;
-        return run_pipe<128, 128, 2, 2, 2, 128, EPI>(tail, st);
-      }
-    }
-    if (EPI != EPI_SWIGLU && round_fill(a.M, a.N, 192) > round_fill(a.M, a.N, 256) + 0.1)
-      return run_pipe<192, 256, 2, 4, 2, 128, EPI>(a, st);
-    if constexpr (EPI == EPI_SWIGLU) {
-      // When the 256 x 256 tiles leave a last round of workgroups at most half full, the FFN
-      // columns of that round go to a second launch of 128 x 128 tiles (64 gate + 64 up
-      // columns, two workgroups per CU), four times as many workgroups each a quarter of the
-      // work: the first launch runs whole rounds only.  Measured on MI355X: 4.3% off the
-      // Qwen3-14B batch-8 gate/up (5.3 rounds), 2.6% off Qwen3-8B batch 16 (7.1 rounds).
-      const int MT = (a.M + 255) / 256, NT = (a.N + 127) / 128, T = MT * NT;
-      const int NT1 = (T / 256) * 256 / MT;  // FFN column tiles of the whole rounds
-      if (T % 256 != 0 && T % 256 <= 128 && NT1 > 0 && NT1 < NT) {
-        GemmArgs head = a, tail = a;
-        head.N = NT1 * 128;
-        const int f0 = NT1 * 128;
-        tail.B0 = (const bf16_t*)a.B0 + (int64_t)f0 * a.K;
-        tail.B1 = (const bf16_t*)a.B1 + (int64_t)f0 * a.K;
-        tail.C = (bf16_t*)a.C + f0;
-        tail.N = a.N - f0;
-        const hipError_t e = run_pipe<256, 256, 2, 4, 2, 128, EPI>(head, st);
-        if (e != hipSuccess) return e;
-        return run_pipe<128, 128, 2, 2, 2, 128, EPI>(tail, st);
-      }
-    }
-    return run_pipe<256, 256, 2, 4, 2, 128, EPI>(a, st);
-  }
   // up to 32 rows (a 17-row verification, the context append, the sampled head's scores): a
   // 32-row tile halves the activation rows each stage loads (target at batch 1: -1.2%)
   if (a.M <= 32 && EPI != EPI_SWIGLU) return run_pipe<32, 128, 2, 2, 3, 128, EPI>(a, st);
@@ -807,28 +664,24 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st) {
     if (a.M > 128 && a.M <= 256) return run_pipe<256, 128, 4, 2, 2, 128, EPI_STORE_F32, 1>(a, st);
     return run_pipe<128, 128, 4, 2, 3, 128, EPI_STORE_F32, 1>(a, st);
   }
-  if (epi == EPI_QKV) {
-    if (amode != A_BF16 || a.M <= 1024 || a.splits != 1 || a.N != (a.qkv.n_q + 2 * a.qkv.n_kv) * 128 ||
-        a.qkv.n_kv < 1 || a.qkv.n_q % a.qkv.n_kv || a.qkv.R < 1 || a.qkv.Rp < a.qkv.R)
+  if (amode == A_BF16 && gemm_large_supported(epi, a)) {
+    if (epi == EPI_TOP2 && a.ldc < (a.N + 127) / 128) return hipErrorInvalidValue;
+    if (epi == EPI_QKV && (a.N != (a.qkv.n_q + 2 * a.qkv.n_kv) * 128 || a.qkv.n_kv < 1 || a.qkv.n_q % a.qkv.n_kv ||
+                           a.qkv.R < 1 || a.qkv.Rp < a.qkv.R))
       return hipErrorInvalidValue;
-    // the same tile choice as the plain projection (192 rows when they fill the rounds better)
-    if (round_fill(a.M, a.N, 192) > round_fill(a.M, a.N, 256) + 0.1)
-      return run_pipe<192, 256, 4, 2, 2, 128, EPI_QKV, 0>(a, st);
-    return run_pipe<256, 256, 4, 2, 2, 128, EPI_QKV, 0>(a, st);
+    return launch_gemm_large(epi, a, st);
   }
   if (epi == EPI_TOP2) {
-    // Top-2 over every branch row from one bf16 plane.  Measured on MI355X at the Qwen3
-    // vocabulary (272 rows a request): up to 1536 rows 192 x 128 tiles (4 waves of 96 x 64, a
-    // 2-deep ring of 80 KB), 22% faster than the large-M tile at 272 rows and 10% at 1088;
-    // beyond, the large-M tile (256 x 256, 8 waves of 128 x 64, two top-2 tiles per
-    // workgroup), 12% faster at 4352 rows.
+    // Top-2 over at most 320 rows from one bf16 plane, measured on MI355X at the Qwen3
+    // vocabulary: 192 x 128 tiles (4 waves of 96 x 64, a 2-deep ring of 80 KB), 22% faster at
+    // 272 rows than 256 x 256; exactly 193-256 rows (the greedy head's ranking at batch 13-16)
+    // take one 256 x 256 tile row (the batch-16 head 587 -> 526 us against two 192-row tiles).
+    // (More rows only with a K that is no multiple of 128.)
     if (amode != A_BF16 || a.ldc < (a.N + 127) / 128) return hipErrorInvalidValue;
-    // exactly 193-256 rows (the greedy head's ranking at batch 13-16): one 256 x 256 tile row
-    // (the batch-16 head 587 -> 526 us against two 192-row tiles)
     if (a.M > 192 && a.M <= 256) return run_pipe<256, 256, 2, 4, 2, 128, EPI_TOP2, 0>(a, st);
-    if (a.M <= 1536) return run_pipe<192, 128, 2, 2, 2, 128, EPI_TOP2, 0>(a, st);
-    return run_pipe<256, 256, 2, 4, 2, 128, EPI_TOP2, 0>(a, st);
+    return run_pipe<192, 128, 2, 2, 2, 128, EPI_TOP2, 0>(a, st);
   }
+  if (epi == EPI_QKV) return hipErrorInvalidValue;  // the large-M kernel's epilogue
   if (amode == A_BF16_FRAG) {
     if (epi == EPI_SWIGLU) return run_adir<EPI_SWIGLU>(a, st);
     if (epi == EPI_STORE_F32) return run_adir<EPI_STORE_F32>(a, st);

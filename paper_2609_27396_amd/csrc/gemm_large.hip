@@ -1,0 +1,597 @@
+// bf16 projections over more than 320 rows: a persistent, software-pipelined GEMM.
+//
+// What bounds a 256 x 256 tile on a CU, per 64-deep K step: the MFMAs (0.98 us at the clock the
+// chip holds), the LDS-DMA of its 64 KB of operands (0.97 us from L2 / Infinity Cache at the
+// rate 256 CUs reach together) and 192 KB of LDS fragment reads (0.42 us).  The three must run
+// side by side, so no wave may ever wait for all of its fragments before its first MFMA:
+//  - A K step has two halves of 32.  The fragments of a half are read, a few at a time, while
+//    the previous half's MFMAs issue; the order is pinned with scheduling barriers and the MFMA
+//    groups run at raised wave priority (without: 605 against 572 us at 4096 x 24576 x 4096).
+//  - One barrier per K step, between the halves: there every fragment of the step has been
+//    read, so its ring slot is free, and the next step's DMA (issued one whole step earlier, the
+//    weights' two) has landed.  The step after is then issued into the freed slot.
+//  - One workgroup per CU walks a list of tiles.  The last K steps of a tile issue the first
+//    ones of the next, so the epilogue and the next tile's first loads overlap.
+// The MFMA operands are swapped (D = B A^T): a lane then holds four consecutive columns of one
+// row, and every epilogue stores 8 or 16 bytes straight from registers, leaving the LDS ring to
+// the DMA.
+// Measured on MI355X, operands not in cache: 4096 x 24576 x 4096 with the SwiGLU epilogue 565 us
+// = 1.46 PFLOP/s, 4624 rows 656 us against 821 for the LDS-pipeline kernel it replaced (which
+// read every fragment of a K step before its first MFMA), 4096 x 4096 x 12288 288 us.
+#include "common.h"
+#include "internal.h"
+
+namespace dpara {
+namespace {
+
+__device__ __forceinline__ float silu_l(float g) {
+  return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f));
+}
+
+__device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
+  return make_uint2((uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16), (uint32_t)f2bf(c) | ((uint32_t)f2bf(d) << 16));
+}
+
+// Sum over the four lanes l, l + 16, l + 32, l + 48 of a wave.
+__device__ __forceinline__ float lanes4_sum(float x) {
+  x += __shfl_xor(x, 16, 64);
+  return x + __shfl_xor(x, 32, 64);
+}
+
+// The work of one launch: `full` tiles of BM x BN over every K split, then, where the last row
+// tile holds few rows, its columns as `tails` tiles of 64 or 128 rows.  A tail costs less than
+// a full tile (tail_cost), so the workgroups without a full tile in the last round take up to
+// two of them each before the rest is dealt to all.
+struct LargePlan {
+  int mtf, NT;      // full row tiles, column tiles
+  int full, tails;  // items
+  int rem, nfree, tails1;
+  int grid;
+};
+
+constexpr int kGroupM = 8;
+
+// B slots of the ring: weights come from HBM, so their loads run a K step further ahead than the
+// activations' (4096 x 4096 x 12288 with operands not in cache: 308 -> 288 us; 192-row tiles
+// 433 -> 391).  The QKV epilogue needs the third slot's LDS for its V^T staging.
+__host__ __device__ constexpr int ring_depth(int epi) { return epi == EPI_QKV ? 2 : 3; }
+
+// Row and column tile of item t among MT x NT tiles: 8 contiguous ranges, one per XCD
+// (workgroups go round-robin over the XCDs), M fastest inside a range or, from 16 row tiles on,
+// inside groups of 8 row tiles (the 32 tiles an XCD runs at once then share 8 A and 4 B tiles).
+__device__ __forceinline__ void large_tile(int t, int total, int MT, int NT, int& s, int& mt, int& nt) {
+  const int per = total >> 3;
+  int L = t;
+  if (t < (per << 3)) L = (t & 7) * per + (t >> 3);
+  s = L / (MT * NT);
+  L -= s * MT * NT;
+  if (MT >= 2 * kGroupM) {
+    const int grp = L / (kGroupM * NT), first = grp * kGroupM;
+    const int gm = min(MT - first, kGroupM), r = L - grp * kGroupM * NT;
+    mt = first + r % gm;
+    nt = r / gm;
+  } else {
+    mt = L % MT;
+    nt = L / MT;
+  }
+}
+
+// Order of one half's MFMAs and fragment reads (FM x FN blocks, groups of GRP MFMAs).  The first
+// FM / 2 row blocks go over all columns, then the others, so that a fragment whose last MFMA
+// comes early (the first part's A, the first columns' B) has one register set and is re-read in
+// the groups after it; the rest have two and are read for the next half in the first groups.
+// 256 x 256: 72 fragment registers instead of 96, which leaves room for the accumulators
+// without spilling.
+template <int FM, int FN>
+struct HalfPlan {
+  static constexpr int GRP = FM * FN % 4 == 0 ? 4 : 2, NG = FM * FN / GRP, LO = FM / 2, HI = FM - LO;
+  static_assert(FM * FN % GRP == 0 && NG >= 2, "whole groups of MFMAs");
+  static constexpr int mi(int t) { return t < LO * FN ? t % LO1 : LO + (t - LO * FN) % HI; }
+  static constexpr int ni(int t) { return t < LO * FN ? t / LO1 : (t - LO * FN) / HI; }
+  static constexpr int LO1 = LO > 0 ? LO : 1;
+  // group of the last MFMA that uses column block n / a row block of the first part
+  static constexpr int last_b(int n) { return (LO * FN + (n + 1) * HI - 1) / GRP; }
+  static constexpr int last_a() { return (LO * FN - 1) / GRP; }
+  static constexpr int singles() {  // B blocks 0 .. singles - 1 have one register set
+    int n = 0;
+    while (n < FN && last_b(n) + 1 <= NG - 2) ++n;
+    return n;
+  }
+  static constexpr int SB = singles(), DB = FN - SB;
+  static constexpr int NBF = SB + 2 * DB, NAF = LO + 2 * HI;
+  static constexpr int bslot(int h, int n) { return n < SB ? n : SB + (n - SB) + h * DB; }
+  static constexpr int aslot(int h, int m) { return m < LO ? m : m + h * HI; }
+  // group before which the next half's fragment is read
+  static constexpr int RATE = (DB + HI + NG - 2) / (NG - 1);
+  static constexpr int read_b(int n) { return n < SB ? last_b(n) + 1 : (n - SB) / RATE; }
+  static constexpr int read_a(int m) { return m < LO ? (last_a() + 1 < NG ? last_a() + 1 : NG - 1) : (DB + m - LO) / RATE; }
+};
+
+// Epilogue of one BM x BN tile whose wave (wm, wn) holds rows m0 + wm * WM .. and columns
+// wn * WN .. of column tile nt: lane (lr, lc) has row .. + mi * 16 + lr and the four columns
+// ni * 16 + lc * 4 .. of every fragment (mi, ni).  stg: 4 KB of LDS of this wave alone.
+template <int BN, int WM, int WN, int WNW, int EPI>
+__device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)[WM / 16][WN / 16], int s, int row0,
+                                               int nt, int wn, int lane, bf16_t* stg) {
+  constexpr int FM = WM / 16, FN = WN / 16;
+  const int lr = lane & 15, lc = lane >> 4;
+  const int row_w = row0 + lr;
+  if constexpr (EPI == EPI_QKV) {
+    static_assert(WN == 128, "one 128-wide head per wave column");
+    // y = x * (1 / sqrt(ss / 128 + eps)) * g over the head's 128 columns (32 in this lane, the
+    // rest in the three lanes 16 apart), then y_d = y_d cos - y_{d+64} sin and
+    // y_{d+64} = y_{d+64} cos + y_d sin, whose operands sit in the same lane.
+    const QkvEpi& e = a.qkv;
+    const int slot = nt * WNW + wn, grp = e.n_q / e.n_kv;
+    if (slot >= e.n_q + 2 * e.n_kv) return;
+    if (slot < e.n_q + e.n_kv) {
+      const bool isq = slot < e.n_q;
+      const float* gain = (isq ? e.qn : e.kn) + lc * 4;
+#pragma unroll
+      for (int mi = 0; mi < FM; ++mi) {
+        __builtin_amdgcn_sched_barrier(0);
+        const int row = row_w + mi * 16, rc = min(row, a.M - 1), b = rc / e.R, rr = rc - b * e.R;
+        if (e.qk_norm) {
+          float ss = 0.f;
+#pragma unroll
+          for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ss += acc[mi][ni][r] * acc[mi][ni][r];
+          ss = lanes4_sum(ss);
+          const float rn = 1.0f / sqrtf(ss / 128.0f + e.eps);
+#pragma unroll
+          for (int ni = 0; ni < FN; ++ni) {
+            const float4 g = *(const float4*)(gain + ni * 16);
+            acc[mi][ni][0] = acc[mi][ni][0] * rn * g.x;
+            acc[mi][ni][1] = acc[mi][ni][1] * rn * g.y;
+            acc[mi][ni][2] = acc[mi][ni][2] * rn * g.z;
+            acc[mi][ni][3] = acc[mi][ni][3] * rn * g.w;
+          }
+        }
+        const float2* cs = e.table + ((int64_t)b * (2 * e.gamma + 1) + row_pos_offset(rr, e.gamma)) * 64 + lc * 4;
+        bf16_t* dst = isq ? (bf16_t*)e.Q + (((int64_t)(b * e.n_kv + slot / grp) * grp + slot % grp) * e.R + rr) * 128
+                          : (bf16_t*)e.Kb + ((int64_t)(b * e.n_kv + (slot - e.n_q)) * e.Rp + rr) * 128;
+        dst += lc * 4;
+#pragma unroll
+        for (int ni = 0; ni < FN / 2; ++ni) {
+          const float4 c01 = *(const float4*)(cs + ni * 16), c23 = *(const float4*)(cs + ni * 16 + 2);
+          const float co[4] = {c01.x, c01.z, c23.x, c23.z}, si[4] = {c01.y, c01.w, c23.y, c23.w};
+          float lo[4], hi[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float l = acc[mi][ni][r], h = acc[mi][ni + FN / 2][r];
+            lo[r] = l * co[r] + -1.f * h * si[r];
+            hi[r] = h * co[r] + 1.f * l * si[r];
+          }
+          if (row < a.M) {
+            *(uint2*)(dst + ni * 16) = pack4(lo[0], lo[1], lo[2], lo[3]);
+            *(uint2*)(dst + ni * 16 + 64) = pack4(hi[0], hi[1], hi[2], hi[3]);
+          }
+        }
+      }
+    } else {
+      // V^T [128][Rp] per request: 32 columns at a time through this wave's LDS, so that a store
+      // covers the wave's consecutive rows of one head dimension
+      const int row = row0 + lane, rc = min(row, a.M - 1), b = rc / e.R;
+      bf16_t* dst = (bf16_t*)e.Vb + (int64_t)(b * e.n_kv + (slot - e.n_q - e.n_kv)) * 128 * e.Rp + (rc - b * e.R);
+#pragma unroll
+      for (int n2 = 0; n2 < FN / 2; ++n2) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) stg[(q * 16 + lc * 4 + r) * 64 + mi * 16 + lr] = f2bf(acc[mi][2 * n2 + q][r]);
+        if (lane < WM && row < a.M)
+#pragma unroll 8
+          for (int d = 0; d < 32; ++d) dst[(int64_t)(n2 * 32 + d) * e.Rp] = stg[d * 64 + lane];
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int mi = 0; mi < FM; ++mi) {
+    __builtin_amdgcn_sched_barrier(0);
+    const int row = row_w + mi * 16;
+    if constexpr (EPI == EPI_TOP2) {
+      static_assert(WN == 128, "one 128-column top-2 tile per wave column");
+      const int tile = nt * WNW + wn, n_tiles = (a.N + 127) / 128;
+      Top3 t{};
+#pragma unroll
+      for (int ni = 0; ni < FN; ++ni) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int col = nt * BN + wn * WN + ni * 16 + lc * 4 + r;
+          if (col < a.N) t.add(argmax_key(acc[mi][ni][r], (uint32_t)col));
+        }
+      }
+#pragma unroll
+      for (int o = 16; o <= 32; o *= 2) {
+        Top3 u;
+        u.k1 = __shfl_xor((unsigned long long)t.k1, o, 64);
+        u.k2 = __shfl_xor((unsigned long long)t.k2, o, 64);
+        u.v3 = __shfl_xor(t.v3, o, 64);
+        t = Top3::merge(t, u);
+      }
+      if (lc == 0 && row < a.M && tile < n_tiles) {
+        uint64_t* o = (uint64_t*)a.C + ((int64_t)row * a.ldc + tile) * 3;
+        o[0] = t.k1;
+        o[1] = t.k2;
+        o[2] = (uint64_t)__float_as_uint(t.v3);
+      }
+      continue;
+    }
+    if (row >= a.M) continue;
+    if constexpr (EPI == EPI_SWIGLU) {
+      const int f0 = nt * (BN / 2) + wn * (WN / 2) + lc * 4;
+      bf16_t* c = (bf16_t*)a.C + (int64_t)row * a.ldc + f0;
+#pragma unroll
+      for (int ni = 0; ni < FN / 2; ++ni) {
+        if (f0 + ni * 16 >= a.N) continue;
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = silu_l(acc[mi][ni][r]) * acc[mi][ni + FN / 2][r];
+        *(uint2*)(c + ni * 16) = pack4(v[0], v[1], v[2], v[3]);
+      }
+    } else {
+      const bool vec = ((a.N | (int)a.ldc) & 3) == 0;  // four columns are one aligned store
+      const int c0 = nt * BN + wn * WN + lc * 4;
+#pragma unroll
+      for (int ni = 0; ni < FN; ++ni) {
+        const f32x4_t v = acc[mi][ni];
+        if constexpr (EPI == EPI_STORE_BF16) {
+          bf16_t* c = (bf16_t*)a.C + (int64_t)row * a.ldc + c0;
+          if (vec) {
+            if (c0 + ni * 16 < a.N) *(uint2*)(c + ni * 16) = pack4(v[0], v[1], v[2], v[3]);
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (c0 + ni * 16 + r < a.N) c[ni * 16 + r] = f2bf(v[r]);
+          }
+        } else {
+          float* c = (float*)a.C + ((int64_t)s * a.M + row) * a.ldc + c0;
+          if (vec) {
+            if (c0 + ni * 16 < a.N) *(f32x4_t*)(c + ni * 16) = v;
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (c0 + ni * 16 + r < a.N) c[ni * 16 + r] = v[r];
+          }
+        }
+      }
+    }
+  }
+}
+
+// A list of n tiles of BM rows (item(i): K split s, first row m0, column tile nt), 8 waves as
+// WMW x WNW; BM and BN multiples of 64, K a multiple of 128 per split.
+template <int BM, int BN, int WMW, int WNW, int NB, int EPI, typename Item>
+__device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item& item, unsigned char* smem) {
+  constexpr int NW = WMW * WNW, WM = BM / WMW, WN = BN / WNW, FM = WM / 16, FN = WN / 16;
+  constexpr int AI = BM / 64, BI = BN / 64, ND = AI + BI;  // 1 KB DMA instructions per wave and K step
+  constexpr int A_SLOT = BM * 128, B_SLOT = BN * 128, B0 = 2 * A_SLOT, RING = 2 * A_SLOT + NB * B_SLOT;
+  using P = HalfPlan<FM, FN>;
+  static_assert(NW == 8, "8 waves");
+  static_assert(EPI != EPI_SWIGLU || FN % 2 == 0, "gate and up fragments in pairs");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WNW, wn = wave % WNW;
+  const int lr = lane & 15, lc = lane >> 4;
+
+  // DMA sources.  One instruction of a wave loads 8 rows of 128 bytes; the eight waves' q-th
+  // loads cover rows 64 q .. of the tile's A or B rows (the same byte offsets for both: lda == K).
+  // Rows past M or N lie outside the buffer descriptor: nothing is read for them, and what their
+  // LDS rows hold only reaches rows and columns the epilogue does not store.  A row's 16-byte
+  // chunk c sits in LDS slot c ^ (row % 8), so fragment reads (16 rows, one chunk) spread over
+  // the banks.
+  const int K2 = a.K * 2, KS = a.K / a.splits, KT = KS / 64;
+  const int lrow = lane >> 3;
+  constexpr int BP = EPI == EPI_SWIGLU ? 2 : 1;  // B parts: gate and up rows
+  int voff[AI > BI / BP ? AI : BI / BP];
+#pragma unroll
+  for (int q = 0; q < (AI > BI / BP ? AI : BI / BP); ++q)
+    voff[q] = (q * 64 + wave * 8 + lrow) * K2 + (((lane & 7) ^ lrow) * 16);
+  const char *pa, *pb[BP];  // the tile the next A load and the next B load belong to
+  unsigned na, nb;          // valid bytes from there
+  int ka = 0, kb = 0;       // and their K steps within it
+  auto a_source = [&](int s, int m0, const char*& p, unsigned& n) {
+    p = (const char*)a.A + (int64_t)m0 * K2 + (int64_t)s * KS * 2;
+    n = (unsigned)(min(BM, a.M - m0) * K2 - s * KS * 2);
+  };
+  auto b_source = [&](int s, int nt, const char* (&p)[BP], unsigned& n) {
+    const int c = nt * (BN / BP), left = min(BN / BP, a.N - c);
+    const void* m = a.B0;
+    int r = c;  // the tile's first row of m
+    if constexpr (EPI == EPI_SWIGLU) {
+      p[BP - 1] = (const char*)a.B1 + (int64_t)c * K2 + (int64_t)s * KS * 2;
+    } else if (a.seg_rows > 0) {  // a tile lies within one segment (gemm_large_supported)
+      const int si = c / a.seg_rows;
+#pragma unroll
+      for (int k = 0; k < kMaxGemmSegs; ++k) m = si == k ? a.seg[k] : m;  // (an indexed argument goes to scratch)
+      r -= si * a.seg_rows;
+    } else if (c >= a.n2) {
+      m = a.B2;
+      r -= a.n2;
+    } else if (c >= a.n1) {
+      m = a.B1;
+      r -= a.n1;
+    }
+    p[0] = (const char*)m + (int64_t)r * K2 + (int64_t)s * KS * 2;
+    n = (unsigned)(left * K2 - s * KS * 2);
+  };
+  // q-th load of A step ka into A slot `as`, or of B step kb into B slot `bs`
+  auto dma = [&](int q, int as, int bs) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const int j = q < AI ? q : q - AI, part = q < AI ? 0 : j / (BI / BP);
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)(q < AI ? pa : pb[part]), 0, (int)(q < AI ? na : nb), 0x00020000);
+    unsigned char* dst = smem + (q < AI ? as * A_SLOT : B0 + bs * B_SLOT) + (wave + NW * j) * 1024;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)dst, 16, voff[q < AI ? q : j % (BI / BP)],
+                                             (q < AI ? ka : kb) * 128, 0, 0);
+#endif
+  };
+
+  // Fragment addresses.  SwiGLU tiles hold BN/2 gate rows, then BN/2 up rows; a wave takes the
+  // same FFN columns of both.
+  const int x0 = (lc ^ (lr & 7)) * 16;
+  constexpr bool kPair = EPI == EPI_SWIGLU;
+  const unsigned char* ra[2];
+  const unsigned char* rb[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    ra[h] = smem + (wm * WM + lr) * 128 + (x0 ^ (h * 64));
+    rb[h] = smem + B0 + (wn * (kPair ? WN / 2 : WN) + lr) * 128 + (x0 ^ (h * 64));
+  }
+  bf16x8_t af[P::NAF], bf[P::NBF];
+  f32x4_t acc[FM][FN];
+  auto read_b = [&](int n, int bs, int h) {
+    const int row = kPair && n >= FN / 2 ? BN / 2 + (n - FN / 2) * 16 : n * 16;
+    bf[P::bslot(h, n)] = *(const bf16x8_t*)(rb[h] + bs * B_SLOT + row * 128);
+  };
+  auto read_a = [&](int m, int as, int h) {
+    af[P::aslot(h, m)] = *(const bf16x8_t*)(ra[h] + as * A_SLOT + m * 2048);
+  };
+  constexpr int DPG = (ND + P::NG - 1) / P::NG;
+  // One half of a K step: the MFMAs of register set h, the fragment reads of the next half
+  // (slots as, bs; set h ^ 1) and, in the second half, the DMA into slots da, db.
+  auto half = [&](int h, int as, int bs, int da, int db) {
+#pragma unroll
+    for (int g = 0; g < P::NG; ++g) {
+#pragma unroll
+      for (int n = 0; n < FN; ++n)
+        if (P::read_b(n) == g) read_b(n, bs, h ^ 1);
+#pragma unroll
+      for (int m = 0; m < FM; ++m)
+        if (P::read_a(m) == g) read_a(m, as, h ^ 1);
+      if (h == 1) {
+#pragma unroll
+        for (int q = g * DPG; q < (g + 1) * DPG && q < ND; ++q) dma(q, da, db);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int t = g * P::GRP; t < (g + 1) * P::GRP; ++t) {
+        const int mi = P::mi(t), ni = P::ni(t);
+        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[P::bslot(h, ni)], af[P::aslot(h, mi)], acc[mi][ni], 0, 0, 0);
+      }
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // steps 0 and 1 (B: NB of them); B step k sits in ring slot k % NB of the whole list's steps
+  int s, m0, nt;  // the tile being computed
+  item(0, s, m0, nt);
+  a_source(s, m0, pa, na);
+  b_source(s, nt, pb, nb);
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+#pragma unroll
+    for (int q = k < 2 ? 0 : AI; q < ND; ++q) dma(q, k, k);
+    if (k < 2) ++ka;
+    ++kb;
+  }
+  wait_vmcnt<AI + BI * (NB - 1)>();
+  __builtin_amdgcn_s_barrier();
+
+  int bs = 0;  // B slot of the current step
+  for (int it = 0; it < n; ++it) {
+    int s1, m1, nt1;  // the next one (the list's end repeats its last tile)
+    item(it + 1 < n ? it + 1 : it, s1, m1, nt1);
+    const char *pa1, *pb1[BP];
+    unsigned na1, nb1;
+    a_source(s1, m1, pa1, na1);
+    b_source(s1, nt1, pb1, nb1);
+#pragma unroll
+    for (int n = 0; n < FN; ++n) read_b(n, bs, 0);
+#pragma unroll
+    for (int m = 0; m < FM; ++m) read_a(m, 0, 0);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int kt = 0; kt < KT; kt += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int bn = bs + 1 == NB ? 0 : bs + 1;
+        __builtin_amdgcn_sched_barrier(0);
+        half(0, u, bs, 0, 0);
+        // Every wave has its fragments of this step, and the next step's DMA has landed: all but
+        // the BI loads of the B step after it (vmcnt counts in order; after an epilogue its stores
+        // are younger than those loads, so the wait is only longer).
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        wait_vmcnt<BI*(NB - 2)>();
+        __builtin_amdgcn_s_barrier();
+        // the last steps of a tile load the next one's first (KT is even and at least 4): scalar
+        // selects, a branch here costs the loop twenty vector registers
+        if (u == 0) {
+          pa = ka == KT ? pa1 : pa;
+          na = ka == KT ? na1 : na;
+          ka = ka == KT ? 0 : ka;
+        }
+        if (u == (NB & 1)) {
+#pragma unroll
+          for (int i = 0; i < BP; ++i) pb[i] = kb == KT ? pb1[i] : pb[i];
+          nb = kb == KT ? nb1 : nb;
+          kb = kb == KT ? 0 : kb;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        half(1, u ^ 1, bn, u, bs);
+        ++ka;
+        ++kb;
+        bs = bn;
+      }
+    }
+    // (the next tile's first fragments are read again after the epilogue: 48 registers less
+    // while it runs)
+    __builtin_amdgcn_sched_barrier(0);
+    large_epilogue<BN, WM, WN, WNW, EPI>(a, acc, s, m0 + wm * WM, nt, wn, lane, (bf16_t*)(smem + RING + wave * 4096));
+    __builtin_amdgcn_sched_barrier(0);
+    s = s1;
+    m0 = m1;
+    nt = nt1;
+  }
+  wait_vmcnt<0>();  // the last loads (the list's end repeats its last tile) have landed
+}
+
+template <int BM, int BN, int EPI, int TAIL>
+__global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs a, LargePlan p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if (a.only_if && *a.only_if == 0) return;
+  const int w = blockIdx.x;
+  constexpr int NB = ring_depth(EPI);
+  debug_poison_lds<(2 * BM + NB * BN) * 128>(smem);
+  // full tiles w, w + grid, ..; then this workgroup's share of the tails
+  const int n_full = w < p.full ? (p.full - w + p.grid - 1) / p.grid : 0;
+  if (n_full > 0)
+    large_tiles<BM, BN, 4, 2, NB, EPI>(a, n_full, [&](int i, int& s, int& m0, int& nt) {
+      int mt;
+      large_tile(w + p.grid * i, p.full, p.mtf, p.NT, s, mt, nt);
+      m0 = mt * BM;
+    }, smem);
+  if constexpr (TAIL > 0) {
+    const int fr = w - p.rem;
+    const int n1 = fr >= 0 && fr < p.tails1 ? (p.tails1 - fr + p.nfree - 1) / p.nfree : 0;
+    const int t2 = p.tails - p.tails1;
+    const int n2 = w < t2 ? (t2 - w + p.grid - 1) / p.grid : 0;
+    if (n1 + n2 == 0) return;
+    __syncthreads();  // the ring is reused
+    // 64 rows: 2 x 4 waves where 64 columns a wave will do (a third fewer LDS reads)
+    constexpr int WNW = TAIL == 64 && BN == 256 && EPI != EPI_QKV && EPI != EPI_TOP2 ? 4 : 2;
+    large_tiles<TAIL, BN, 8 / WNW, WNW, NB, EPI>(
+        a, n1 + n2, [&](int i, int& s, int& m0, int& nt) {
+          const int t = i < n1 ? fr + p.nfree * i : p.tails1 + w + p.grid * (i - n1);
+          s = t / p.NT;
+          nt = t - s * p.NT;
+          m0 = p.mtf * BM;
+        }, smem);
+  }
+}
+
+constexpr int kCus = 256;
+
+// Rows of the tail tiles (0: the last row tile runs as a full one) and their cost against a full
+// tile: a 64-row tile is bound by its weight loads (36 KB of a full tile's 64 KB a K step).
+int tail_rows(int M, int BM) {
+  const int left = (M - 1) % BM + 1;
+  return left <= 64 ? 64 : left <= 128 && BM > 128 ? 128 : 0;
+}
+double tail_cost(int rows, int BM) { return rows == 64 ? (BM == 256 ? 0.45 : 0.55) : (BM == 256 ? 0.65 : 0.8); }
+
+LargePlan large_plan(int M, int NT, int BM, int S) {
+  LargePlan p{};
+  const int tail = tail_rows(M, BM);
+  p.NT = NT;
+  p.mtf = (M + BM - 1) / BM - (tail ? 1 : 0);
+  p.full = p.mtf * NT * S;
+  p.tails = tail ? NT * S : 0;
+  p.grid = p.full + p.tails < kCus ? p.full + p.tails : kCus;
+  p.rem = p.full % p.grid;
+  p.nfree = p.grid - p.rem;
+  const int cap = tail == 64 ? 2 : 1;
+  p.tails1 = p.tails < cap * p.nfree ? p.tails : cap * p.nfree;
+  return p;
+}
+
+// Rounds the launch takes, in units of one full tile.
+double large_rounds(int M, int NT, int BM, int S) {
+  const LargePlan p = large_plan(M, NT, BM, S);
+  const double tc = tail_cost(tail_rows(M, BM), BM);
+  const int whole = p.full / p.grid, n1 = (p.tails1 + p.nfree - 1) / p.nfree, t2 = p.tails - p.tails1;
+  double r = whole + (p.rem > 0 ? 1.0 : 0.0);
+  if (whole + n1 * tc > r) r = whole + n1 * tc;
+  return r + (t2 + p.grid - 1) / p.grid * tc;
+}
+
+template <int BM, int BN, int EPI, int TAIL>
+hipError_t run_large_tail(const GemmArgs& a, const LargePlan& p, hipStream_t st) {
+  constexpr int lds = (2 * BM + ring_depth(EPI) * BN) * 128 + (EPI == EPI_QKV ? 8 * 4096 : 0);
+  static_assert(lds <= 163840, "LDS");
+  auto kern = gemm_large_kernel<BM, BN, EPI, TAIL>;
+  static const hipError_t attr =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kern, dim3(p.grid), dim3(512), lds, st, a, p);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int EPI>
+hipError_t run_large(const GemmArgs& a, hipStream_t st) {
+  constexpr int COLS = EPI == EPI_SWIGLU ? BN / 2 : BN;
+  const LargePlan p = large_plan(a.M, (a.N + COLS - 1) / COLS, BM, a.splits);
+  switch (tail_rows(a.M, BM)) {
+    case 64: return run_large_tail<BM, BN, EPI, 64>(a, p, st);
+    case 128: return run_large_tail<BM, BN, EPI, 128>(a, p, st);
+    default: return run_large_tail<BM, BN, EPI, 0>(a, p, st);
+  }
+}
+
+template <int EPI>
+hipError_t pick_large(const GemmArgs& a, hipStream_t st) {
+  // The tile with the least estimated time: rounds times a tile's time per K step, 1.46 us for
+  // 256 x 256 and 1.02 for 192 x 256 and 256 x 192 (measured over 12288-deep tiles).
+  constexpr int half = EPI == EPI_SWIGLU ? 2 : 1;
+  auto cost = [&](int BM, int BN, double t) {
+    return t * large_rounds(a.M, (a.N + BN / half - 1) / (BN / half), BM, a.splits);
+  };
+  const double c0 = cost(256, 256, 1.46), c1 = cost(192, 256, 1.02);
+  if constexpr (EPI == EPI_STORE_F32) {
+    const double c2 = cost(256, 192, 1.02);
+    if (a.seg_rows == 0 && a.n1 >= a.N && c2 < c0 && c2 < c1) return run_large<256, 192, EPI>(a, st);
+  }
+  if (c1 < c0) return run_large<192, 256, EPI>(a, st);
+  return run_large<256, 256, EPI>(a, st);
+}
+
+}  // namespace
+
+bool gemm_large_supported(int epi, const GemmArgs& a) {
+  if (a.M <= 320 || a.splits < 1 || a.K % (128 * a.splits) != 0 || a.K / a.splits < 256 || a.lda != a.K)
+    return false;
+  if (a.splits > 1 && epi != EPI_STORE_F32) return false;
+  if (epi != EPI_SWIGLU) {  // a 256-column tile comes from one weight segment
+    if (a.seg_rows % 256 != 0) return false;
+    if (a.seg_rows == 0 && ((a.n1 < a.N && a.n1 % 256 != 0) || (a.n2 < a.N && a.n2 % 256 != 0))) return false;
+  }
+  switch (epi) {
+    case EPI_SWIGLU: return a.N % 8 == 0 && a.ldc % 4 == 0;
+    case EPI_STORE_F32:
+    case EPI_STORE_BF16:
+    case EPI_TOP2:
+    case EPI_QKV: return true;
+    default: return false;
+  }
+}
+
+hipError_t launch_gemm_large(int epi, const GemmArgs& a, hipStream_t st) {
+  if (!gemm_large_supported(epi, a)) return hipErrorInvalidValue;
+  switch (epi) {
+    case EPI_SWIGLU: return pick_large<EPI_SWIGLU>(a, st);
+    case EPI_STORE_F32: return pick_large<EPI_STORE_F32>(a, st);
+    case EPI_STORE_BF16: return run_large<256, 256, EPI_STORE_BF16>(a, st);
+    case EPI_TOP2: return run_large<256, 256, EPI_TOP2>(a, st);
+    default: return pick_large<EPI_QKV>(a, st);
+  }
+}
+
+}  // namespace dpara

@@ -81,6 +81,10 @@ struct GemmArgs {
 
 constexpr int kMaxGemmSegs = 16;
 hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st);
+// The persistent kernel for more than 320 bf16 rows (gemm_large.hip): whether it takes this
+// call, and its launch.
+bool gemm_large_supported(int epi, const GemmArgs& a);
+hipError_t launch_gemm_large(int epi, const GemmArgs& a, hipStream_t st);
 // Split-K factor launch_gemm uses for a bf16 fp32-store GEMM of this shape (1 = no split).
 // The consumer of C sums the S planes in order 0..S-1.
 int gemm_splits(int amode, int epi, int M, int N, int K);
