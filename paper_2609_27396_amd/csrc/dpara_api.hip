@@ -172,8 +172,11 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
   // (up to 64 rows the row-major LDS pipeline streams the weights faster: the 36-layer target
   // at batch 1, 5.2-5.4 -> 4.8 ms).
   p.afrag = c->dtype == DPARA_BF16 && p.M > 64 && p.M <= 320 && H % 256 == 0;
-  p.s_qkv = gemm_splits(p.afrag ? A_BF16_FRAG : amode, EPI_STORE_F32, p.M, (nq + 2 * nkv) * hd, H);
-  p.qkv_fused = c->dtype == DPARA_BF16 && hd == 128 && p.M > 1024 && p.s_qkv == 1 && H % 128 == 0;
+  // Above 320 rows the large-M kernel's epilogue applies q/k-norm and RoPE (128-wide heads; a
+  // 256-column tile within one of W_q, W_k, W_v); otherwise split planes and the q/k-norm pass.
+  const int kv_seg = nkv * hd;  // divides n_q heads' columns too
+  p.qkv_fused = c->dtype == DPARA_BF16 && hd == 128 && p.M > 320 && H % 128 == 0 && H >= 256 && kv_seg % 256 == 0;
+  p.s_qkv = p.qkv_fused ? 1 : gemm_splits(p.afrag ? A_BF16_FRAG : amode, EPI_STORE_F32, p.M, (nq + 2 * nkv) * hd, H, kv_seg);
   p.s_o = gemm_splits(amode, EPI_STORE_F32, p.M, H, nq * hd);
   p.s_down = gemm_splits(amode, EPI_STORE_F32, p.M, H, c->ffn);
   const size_t M = p.M;
@@ -345,7 +348,7 @@ int run_decoder(const dpara_config_t* cfg, const dpara_layer_weights_t* layers, 
     q.ldc = q.N;
     q.splits = p.s_qkv;
     if (p.qkv_fused) {
-      // above 1024 rows (no split-K) the GEMM's epilogue applies q/k-norm and RoPE itself and
+      // above 320 rows (no split-K) the GEMM's epilogue applies q/k-norm and RoPE itself and
       // writes Q, K, V^T in bf16: the float32 Q|K|V never leaves the chip
       q.qkv.R = R;
       q.qkv.Rp = p.Rp;
@@ -592,7 +595,11 @@ int dpara_ctx_append(const dpara_config_t* cfg, const dpara_weights_t* w, const 
       g.K = H;
       g.C = at<void>(ws, p.KV32);
       g.ldc = g.N;
-      g.splits = gemm_splits(dt == DPARA_BF16 ? A_BF16 : A_F32, EPI_STORE_F32, g.M, g.N, g.K);
+      g.splits = gemm_splits(dt == DPARA_BF16 ? A_BF16 : A_F32, EPI_STORE_F32, g.M, g.N, g.K, g.seg_rows);
+      if (g.M > 320) {  // the planes fit the region of make_plan
+        const int kv_rows = batch * p.CH > 16 * 320 ? batch * p.CH : 16 * 320;
+        while (g.splits > 1 && g.splits * g.M > kv_rows) --g.splits;
+      }
       {
         Phase ph("append_gemm", st);
         HIP_TRY(launch_gemm(dt == DPARA_BF16 ? A_BF16 : A_F32, EPI_STORE_F32, g, st), "append kv gemm");
@@ -1044,6 +1051,8 @@ int dpara_fuse_features(const dpara_config_t* cfg, const dpara_fusion_weights_t*
     g.C = planes;
     g.ldc = H;
     g.splits = gemm_splits(amode, EPI_STORE_F32, m, H, K);
+    // the planes of a pass of more than 320 rows fit the space 16 planes of 320 take
+    while (m > 320 && g.splits > 1 && g.splits * m > 16 * 320) --g.splits;
     {
       Phase ph("fuse_gemm", st);
       HIP_TRY(launch_gemm(amode, EPI_STORE_F32, g, st), "fusion gemm");

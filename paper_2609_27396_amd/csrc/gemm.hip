@@ -616,7 +616,7 @@ hipError_t run_bf16(const GemmArgs& a, hipStream_t st) {
 
 }  // namespace
 
-int gemm_splits(int amode, int epi, int M, int N, int K) {
+int gemm_splits(int amode, int epi, int M, int N, int K, int seg) {
   if (amode == A_BF16_FRAG) {
     // 96-column tiles; K steps of each split a multiple of the 4-deep ring
     if (epi != EPI_STORE_F32) return 1;
@@ -625,7 +625,8 @@ int gemm_splits(int amode, int epi, int M, int N, int K) {
     while (S < 16 && NT * S * 2 <= 256 && K % (256 * S * 2) == 0) S *= 2;
     return S;
   }
-  if (amode != A_BF16 || epi != EPI_STORE_F32 || M > 320) return 1;
+  if (amode != A_BF16 || epi != EPI_STORE_F32) return 1;
+  if (M > 320) return K % 128 == 0 && K >= 256 && seg % 256 == 0 ? gemm_large_splits(M, N, K) : 1;
   const int NT = (N + 127) / 128;
   const int max_wg = M <= 64 ? 512 : 256;  // the M <= 64 tile fits two workgroups per CU
   int S = 1;

@@ -53,8 +53,12 @@ constexpr int kGroupM = 8;
 
 // B slots of the ring: weights come from HBM, so their loads run a K step further ahead than the
 // activations' (4096 x 4096 x 12288 with operands not in cache: 308 -> 288 us; 192-row tiles
-// 433 -> 391).  The QKV epilogue needs the third slot's LDS for its V^T staging.
-__host__ __device__ constexpr int ring_depth(int epi) { return epi == EPI_QKV ? 2 : 3; }
+// 433 -> 391).  The QKV epilogue's V^T staging (2 KB a wave) leaves no room for the third slot
+// at 256 rows.  A tail tile's K step is short (36 KB of loads), so there both operands run two or
+// three steps ahead.
+__host__ __device__ constexpr int ring_depth(int epi, int bm) { return epi == EPI_QKV && bm == 256 ? 2 : 3; }
+__host__ __device__ constexpr int tail_depth(int epi, int tail) { return epi == EPI_QKV || tail == 128 ? 3 : 4; }
+constexpr int kStageWave = 2048;
 
 // Row and column tile of item t among MT x NT tiles: 8 contiguous ranges, one per XCD
 // (workgroups go round-robin over the XCDs), M fastest inside a range or, from 16 row tiles on,
@@ -109,7 +113,7 @@ struct HalfPlan {
 
 // Epilogue of one BM x BN tile whose wave (wm, wn) holds rows m0 + wm * WM .. and columns
 // wn * WN .. of column tile nt: lane (lr, lc) has row .. + mi * 16 + lr and the four columns
-// ni * 16 + lc * 4 .. of every fragment (mi, ni).  stg: 4 KB of LDS of this wave alone.
+// ni * 16 + lc * 4 .. of every fragment (mi, ni).  stg: kStageWave bytes of LDS of this wave alone.
 template <int BN, int WM, int WN, int WNW, int EPI>
 __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)[WM / 16][WN / 16], int s, int row0,
                                                int nt, int wn, int lane, bf16_t* stg) {
@@ -170,22 +174,20 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
         }
       }
     } else {
-      // V^T [128][Rp] per request: 32 columns at a time through this wave's LDS, so that a store
+      // V^T [128][Rp] per request: 16 columns at a time through this wave's LDS, so that a store
       // covers the wave's consecutive rows of one head dimension
       const int row = row0 + lane, rc = min(row, a.M - 1), b = rc / e.R;
       bf16_t* dst = (bf16_t*)e.Vb + (int64_t)(b * e.n_kv + (slot - e.n_q - e.n_kv)) * 128 * e.Rp + (rc - b * e.R);
 #pragma unroll
-      for (int n2 = 0; n2 < FN / 2; ++n2) {
+      for (int ni = 0; ni < FN; ++ni) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
+        for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
-          for (int mi = 0; mi < FM; ++mi)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) stg[(q * 16 + lc * 4 + r) * 64 + mi * 16 + lr] = f2bf(acc[mi][2 * n2 + q][r]);
+          for (int r = 0; r < 4; ++r) stg[(lc * 4 + r) * 64 + mi * 16 + lr] = f2bf(acc[mi][ni][r]);
         if (lane < WM && row < a.M)
 #pragma unroll 8
-          for (int d = 0; d < 32; ++d) dst[(int64_t)(n2 * 32 + d) * e.Rp] = stg[d * 64 + lane];
+          for (int d = 0; d < 16; ++d) dst[(int64_t)(ni * 16 + d) * e.Rp] = stg[d * 64 + lane];
       }
     }
     return;
@@ -266,12 +268,17 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
 }
 
 // A list of n tiles of BM rows (item(i): K split s, first row m0, column tile nt), 8 waves as
-// WMW x WNW; BM and BN multiples of 64, K a multiple of 128 per split.
-template <int BM, int BN, int WMW, int WNW, int NB, int EPI, typename Item>
+// WMW x WNW; BM and BN multiples of 64, K a multiple of 128, at least
+// 256 per split.
+template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, typename Item>
 __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item& item, unsigned char* smem) {
   constexpr int NW = WMW * WNW, WM = BM / WMW, WN = BN / WNW, FM = WM / 16, FN = WN / 16;
   constexpr int AI = BM / 64, BI = BN / 64, ND = AI + BI;  // 1 KB DMA instructions per wave and K step
-  constexpr int A_SLOT = BM * 128, B_SLOT = BN * 128, B0 = 2 * A_SLOT, RING = 2 * A_SLOT + NB * B_SLOT;
+  constexpr int A_SLOT = BM * 128, B_SLOT = BN * 128, B0 = NA * A_SLOT, RING = NA * A_SLOT + NB * B_SLOT;
+  // loads a step's barrier may leave in flight: those issued after the next step's (vmcnt counts
+  // in order)
+  static_assert(NA == NB || (NA == 2 && NB == 3), "ring depths");
+  constexpr int LATER = NA == NB ? (NB - 2) * ND : BI;
   using P = HalfPlan<FM, FN>;
   static_assert(NW == 8, "8 waves");
   static_assert(EPI != EPI_SWIGLU || FN % 2 == 0, "gate and up fragments in pairs");
@@ -285,7 +292,7 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
   // LDS rows hold only reaches rows and columns the epilogue does not store.  A row's 16-byte
   // chunk c sits in LDS slot c ^ (row % 8), so fragment reads (16 rows, one chunk) spread over
   // the banks.
-  const int K2 = a.K * 2, KS = a.K / a.splits, KT = KS / 64;
+  const int K2 = a.K * 2;
   const int lrow = lane >> 3;
   constexpr int BP = EPI == EPI_SWIGLU ? 2 : 1;  // B parts: gate and up rows
   int voff[AI > BI / BP ? AI : BI / BP];
@@ -295,16 +302,18 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
   const char *pa, *pb[BP];  // the tile the next A load and the next B load belong to
   unsigned na, nb;          // valid bytes from there
   int ka = 0, kb = 0;       // and their K steps within it
+  // split s covers the 128-deep K units [s U / S, (s + 1) U / S), U = K / 128
+  auto k_byte = [&](int s) { return (int)((int64_t)(a.K / 128) * s / a.splits) * 256; };
   auto a_source = [&](int s, int m0, const char*& p, unsigned& n) {
-    p = (const char*)a.A + (int64_t)m0 * K2 + (int64_t)s * KS * 2;
-    n = (unsigned)(min(BM, a.M - m0) * K2 - s * KS * 2);
+    p = (const char*)a.A + (int64_t)m0 * K2 + k_byte(s);
+    n = (unsigned)(min(BM, a.M - m0) * K2 - k_byte(s));
   };
   auto b_source = [&](int s, int nt, const char* (&p)[BP], unsigned& n) {
     const int c = nt * (BN / BP), left = min(BN / BP, a.N - c);
     const void* m = a.B0;
     int r = c;  // the tile's first row of m
     if constexpr (EPI == EPI_SWIGLU) {
-      p[BP - 1] = (const char*)a.B1 + (int64_t)c * K2 + (int64_t)s * KS * 2;
+      p[BP - 1] = (const char*)a.B1 + (int64_t)c * K2 + k_byte(s);
     } else if (a.seg_rows > 0) {  // a tile lies within one segment (gemm_large_supported)
       const int si = c / a.seg_rows;
 #pragma unroll
@@ -317,8 +326,8 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
       m = a.B1;
       r -= a.n1;
     }
-    p[0] = (const char*)m + (int64_t)r * K2 + (int64_t)s * KS * 2;
-    n = (unsigned)(left * K2 - s * KS * 2);
+    p[0] = (const char*)m + (int64_t)r * K2 + k_byte(s);
+    n = (unsigned)(left * K2 - k_byte(s));
   };
   // q-th load of A step ka into A slot `as`, or of B step kb into B slot `bs`
   auto dma = [&](int q, int as, int bs) {
@@ -379,7 +388,8 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
     }
   };
 
-  // steps 0 and 1 (B: NB of them); B step k sits in ring slot k % NB of the whole list's steps
+  // the first NA steps of A and NB of B; a step's ring slot is its number, over the whole list's
+  // steps, mod NA or NB
   int s, m0, nt;  // the tile being computed
   item(0, s, m0, nt);
   a_source(s, m0, pa, na);
@@ -387,14 +397,14 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
 #pragma unroll
   for (int k = 0; k < NB; ++k) {
 #pragma unroll
-    for (int q = k < 2 ? 0 : AI; q < ND; ++q) dma(q, k, k);
-    if (k < 2) ++ka;
+    for (int q = k < NA ? 0 : AI; q < ND; ++q) dma(q, k, k);
+    if (k < NA) ++ka;
     ++kb;
   }
-  wait_vmcnt<AI + BI * (NB - 1)>();
+  wait_vmcnt<AI*(NA - 1) + BI * (NB - 1)>();
   __builtin_amdgcn_s_barrier();
 
-  int bs = 0;  // B slot of the current step
+  int as = 0, bs = 0;  // slots of the current step
   for (int it = 0; it < n; ++it) {
     int s1, m1, nt1;  // the next one (the list's end repeats its last tile)
     item(it + 1 < n ? it + 1 : it, s1, m1, nt1);
@@ -402,10 +412,11 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
     unsigned na1, nb1;
     a_source(s1, m1, pa1, na1);
     b_source(s1, nt1, pb1, nb1);
+    const int KT = (k_byte(s + 1) - k_byte(s)) / 128;
 #pragma unroll
-    for (int n = 0; n < FN; ++n) read_b(n, bs, 0);
+    for (int j = 0; j < FN; ++j) read_b(j, bs, 0);
 #pragma unroll
-    for (int m = 0; m < FM; ++m) read_a(m, 0, 0);
+    for (int i = 0; i < FM; ++i) read_a(i, as, 0);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -413,18 +424,18 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
     for (int kt = 0; kt < KT; kt += 2) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const int bn = bs + 1 == NB ? 0 : bs + 1;
+        if (NA == 2) as = u;  // (KT is even: a constant)
+        const int an = as + 1 == NA ? 0 : as + 1, bn = bs + 1 == NB ? 0 : bs + 1;
         __builtin_amdgcn_sched_barrier(0);
-        half(0, u, bs, 0, 0);
-        // Every wave has its fragments of this step, and the next step's DMA has landed: all but
-        // the BI loads of the B step after it (vmcnt counts in order; after an epilogue its stores
-        // are younger than those loads, so the wait is only longer).
+        half(0, as, bs, 0, 0);
+        // Every wave has its fragments of this step, and the next step's DMA has landed (after an
+        // epilogue its stores are younger than the loads, so the wait is only longer).
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        wait_vmcnt<BI*(NB - 2)>();
+        wait_vmcnt<LATER>();
         __builtin_amdgcn_s_barrier();
         // the last steps of a tile load the next one's first (KT is even and at least 4): scalar
         // selects, a branch here costs the loop twenty vector registers
-        if (u == 0) {
+        if (u == (NA & 1)) {
           pa = ka == KT ? pa1 : pa;
           na = ka == KT ? na1 : na;
           ka = ka == KT ? 0 : ka;
@@ -436,16 +447,17 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
           kb = kb == KT ? 0 : kb;
         }
         __builtin_amdgcn_sched_barrier(0);
-        half(1, u ^ 1, bn, u, bs);
+        half(1, an, bn, as, bs);
         ++ka;
         ++kb;
+        as = an;
         bs = bn;
       }
     }
     // (the next tile's first fragments are read again after the epilogue: 48 registers less
     // while it runs)
     __builtin_amdgcn_sched_barrier(0);
-    large_epilogue<BN, WM, WN, WNW, EPI>(a, acc, s, m0 + wm * WM, nt, wn, lane, (bf16_t*)(smem + RING + wave * 4096));
+    large_epilogue<BN, WM, WN, WNW, EPI>(a, acc, s, m0 + wm * WM, nt, wn, lane, (bf16_t*)(smem + RING + wave * kStageWave));
     __builtin_amdgcn_sched_barrier(0);
     s = s1;
     m0 = m1;
@@ -459,12 +471,12 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs a, LargePla
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (a.only_if && *a.only_if == 0) return;
   const int w = blockIdx.x;
-  constexpr int NB = ring_depth(EPI);
+  constexpr int NB = ring_depth(EPI, BM);
   debug_poison_lds<(2 * BM + NB * BN) * 128>(smem);
   // full tiles w, w + grid, ..; then this workgroup's share of the tails
   const int n_full = w < p.full ? (p.full - w + p.grid - 1) / p.grid : 0;
   if (n_full > 0)
-    large_tiles<BM, BN, 4, 2, NB, EPI>(a, n_full, [&](int i, int& s, int& m0, int& nt) {
+    large_tiles<BM, BN, 4, 2, 2, NB, EPI>(a, n_full, [&](int i, int& s, int& m0, int& nt) {
       int mt;
       large_tile(w + p.grid * i, p.full, p.mtf, p.NT, s, mt, nt);
       m0 = mt * BM;
@@ -476,9 +488,10 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs a, LargePla
     const int n2 = w < t2 ? (t2 - w + p.grid - 1) / p.grid : 0;
     if (n1 + n2 == 0) return;
     __syncthreads();  // the ring is reused
+    constexpr int TD = tail_depth(EPI, TAIL);
     // 64 rows: 2 x 4 waves where 64 columns a wave will do (a third fewer LDS reads)
     constexpr int WNW = TAIL == 64 && BN == 256 && EPI != EPI_QKV && EPI != EPI_TOP2 ? 4 : 2;
-    large_tiles<TAIL, BN, 8 / WNW, WNW, NB, EPI>(
+    large_tiles<TAIL, BN, 8 / WNW, WNW, TD, TD, EPI>(
         a, n1 + n2, [&](int i, int& s, int& m0, int& nt) {
           const int t = i < n1 ? fr + p.nfree * i : p.tails1 + w + p.grid * (i - n1);
           s = t / p.NT;
@@ -496,7 +509,7 @@ int tail_rows(int M, int BM) {
   const int left = (M - 1) % BM + 1;
   return left <= 64 ? 64 : left <= 128 && BM > 128 ? 128 : 0;
 }
-double tail_cost(int rows, int BM) { return rows == 64 ? (BM == 256 ? 0.45 : 0.55) : (BM == 256 ? 0.65 : 0.8); }
+double tail_cost(int rows, int BM) { return rows == 64 ? (BM == 256 ? 0.5 : 0.65) : (BM == 256 ? 0.65 : 0.8); }
 
 LargePlan large_plan(int M, int NT, int BM, int S) {
   LargePlan p{};
@@ -513,19 +526,44 @@ LargePlan large_plan(int M, int NT, int BM, int S) {
   return p;
 }
 
-// Rounds the launch takes, in units of one full tile.
-double large_rounds(int M, int NT, int BM, int S) {
+// Estimated time of the launch, us (operands from HBM; fitted to measurements on MI355X over 400 to
+// 4624 rows, within about 8%): a 64-deep K step of a 256 x 256 tile takes 1.44, of 192 x 256 and
+// 256 x 192 1.18; each tile 1.5 more.  A round that fills only part of the CUs runs its tiles
+// up to 22% faster.
+double large_time(int M, int NT, int BM, int BN, int S, int K) {
   const LargePlan p = large_plan(M, NT, BM, S);
+  const int steps = (K / 128 + S - 1) / S * 2;
+  const double t = (BM == 256 && BN == 256 ? 1.44 : 1.18) * steps + 1.5;
   const double tc = tail_cost(tail_rows(M, BM), BM);
   const int whole = p.full / p.grid, n1 = (p.tails1 + p.nfree - 1) / p.nfree, t2 = p.tails - p.tails1;
-  double r = whole + (p.rem > 0 ? 1.0 : 0.0);
+  const double last = 0.78 + 0.22 * (p.rem + tc * p.tails1) / kCus;
+  double r = whole * (p.grid < kCus ? 0.78 + 0.22 * p.grid / kCus : 1.0) + (p.rem > 0 ? last : 0.0);
   if (whole + n1 * tc > r) r = whole + n1 * tc;
-  return r + (t2 + p.grid - 1) / p.grid * tc;
+  return (r + (t2 + p.grid - 1) / p.grid * tc) * t;
+}
+
+struct LargeTile {
+  int BM, BN;
+  double us;
+};
+// The tile with the least estimated time.  narrow: 256 x 192 is available.
+LargeTile large_choice(int M, int N, int K, int S, int cols_per_256, bool narrow) {
+  auto nt = [&](int bn) { const int c = bn * cols_per_256 / 256; return (N + c - 1) / c; };
+  LargeTile best{256, 256, large_time(M, nt(256), 256, 256, S, K)};
+  const double t1 = large_time(M, nt(256), 192, 256, S, K);
+  if (t1 < best.us) best = {192, 256, t1};
+  if (narrow) {
+    const double t2 = large_time(M, nt(192), 256, 192, S, K);
+    if (t2 < best.us) best = {256, 192, t2};
+  }
+  return best;
 }
 
 template <int BM, int BN, int EPI, int TAIL>
 hipError_t run_large_tail(const GemmArgs& a, const LargePlan& p, hipStream_t st) {
-  constexpr int lds = (2 * BM + ring_depth(EPI) * BN) * 128 + (EPI == EPI_QKV ? 8 * 4096 : 0);
+  constexpr int ring = (2 * BM + ring_depth(EPI, BM) * BN) * 128;
+  constexpr int tail = TAIL ? tail_depth(EPI, TAIL) * (TAIL + BN) * 128 : 0;
+  constexpr int lds = (ring > tail ? ring : tail) + (EPI == EPI_QKV ? 8 * kStageWave : 0);
   static_assert(lds <= 163840, "LDS");
   auto kern = gemm_large_kernel<BM, BN, EPI, TAIL>;
   static const hipError_t attr =
@@ -548,26 +586,18 @@ hipError_t run_large(const GemmArgs& a, hipStream_t st) {
 
 template <int EPI>
 hipError_t pick_large(const GemmArgs& a, hipStream_t st) {
-  // The tile with the least estimated time: rounds times a tile's time per K step, 1.46 us for
-  // 256 x 256 and 1.02 for 192 x 256 and 256 x 192 (measured over 12288-deep tiles).
-  constexpr int half = EPI == EPI_SWIGLU ? 2 : 1;
-  auto cost = [&](int BM, int BN, double t) {
-    return t * large_rounds(a.M, (a.N + BN / half - 1) / (BN / half), BM, a.splits);
-  };
-  const double c0 = cost(256, 256, 1.46), c1 = cost(192, 256, 1.02);
-  if constexpr (EPI == EPI_STORE_F32) {
-    const double c2 = cost(256, 192, 1.02);
-    if (a.seg_rows == 0 && a.n1 >= a.N && c2 < c0 && c2 < c1) return run_large<256, 192, EPI>(a, st);
-  }
-  if (c1 < c0) return run_large<192, 256, EPI>(a, st);
+  const bool narrow = EPI == EPI_STORE_F32 && a.seg_rows == 0 && a.n1 >= a.N;
+  const LargeTile t = large_choice(a.M, a.N, a.K, a.splits, EPI == EPI_SWIGLU ? 128 : 256, narrow);
+  if constexpr (EPI == EPI_STORE_F32)
+    if (t.BN == 192) return run_large<256, 192, EPI>(a, st);
+  if (t.BM == 192) return run_large<192, 256, EPI>(a, st);
   return run_large<256, 256, EPI>(a, st);
 }
 
 }  // namespace
 
 bool gemm_large_supported(int epi, const GemmArgs& a) {
-  if (a.M <= 320 || a.splits < 1 || a.K % (128 * a.splits) != 0 || a.K / a.splits < 256 || a.lda != a.K)
-    return false;
+  if (a.M <= 320 || a.splits < 1 || a.K % 128 != 0 || a.K / 128 < 2 * a.splits || a.lda != a.K) return false;
   if (a.splits > 1 && epi != EPI_STORE_F32) return false;
   if (epi != EPI_SWIGLU) {  // a 256-column tile comes from one weight segment
     if (a.seg_rows % 256 != 0) return false;
@@ -581,6 +611,21 @@ bool gemm_large_supported(int epi, const GemmArgs& a) {
     case EPI_QKV: return true;
     default: return false;
   }
+}
+
+int gemm_large_splits(int M, int N, int K) {
+  // Least estimated time: the GEMM and, for each plane, its store and the consumer's read (about
+  // 3.5 and 4 TB/s).  867 x 4096 x 12288: 195 us as one plane, 84 as three.
+  int best = 1;
+  double us = 1e30;
+  for (int S = 1; S <= 8 && K / 128 >= 2 * S; ++S) {
+    const double t = large_choice(M, N, K, S, 256, true).us + S * (double)M * N * 4.0 * (1 / 3.5e6 + 1 / 4e6);
+    if (t < us) {
+      us = t;
+      best = S;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_gemm_large(int epi, const GemmArgs& a, hipStream_t st) {

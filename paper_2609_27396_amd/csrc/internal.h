@@ -76,7 +76,7 @@ struct GemmArgs {
   const int* only_if = nullptr;  // non-NULL: every workgroup returns at once unless *only_if != 0
   int seg_rows = 0;               // > 0: B rows from seg[] (N <= kMaxGemmSegs * seg_rows)
   const void* seg[16] = {};
-  QkvEpi qkv{};  // EPI_QKV only (bf16, head_dim 128, more than 1024 rows, no split-K)
+  QkvEpi qkv{};  // EPI_QKV only (bf16, head_dim 128, gemm_large_supported(), no split-K)
 };
 
 constexpr int kMaxGemmSegs = 16;
@@ -85,9 +85,11 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st);
 // call, and its launch.
 bool gemm_large_supported(int epi, const GemmArgs& a);
 hipError_t launch_gemm_large(int epi, const GemmArgs& a, hipStream_t st);
+int gemm_large_splits(int M, int N, int K);  // split-K planes of its float32 store
 // Split-K factor launch_gemm uses for a bf16 fp32-store GEMM of this shape (1 = no split).
-// The consumer of C sums the S planes in order 0..S-1.
-int gemm_splits(int amode, int epi, int M, int N, int K);
+// The consumer of C sums the S planes in order 0..S-1.  seg: greatest common divisor of the
+// boundaries of the weight's row segments (0: one segment).
+int gemm_splits(int amode, int epi, int M, int N, int K, int seg = 0);
 
 // ---------------------------------------------------------------- attention
 struct AttnArgs {
