@@ -35,7 +35,7 @@ PEAK_HBM_GBS = 8000.0
 PEAK_BF16_TFLOPS = 2500.0
 PEAK_F32_TFLOPS = 157.3
 COPY_PROBE_BYTES = 256 << 20
-GATEUP_KERNEL_SMALL_M = "gemm_adir_kernel<2, 4, 0>"  # the gate/up SwiGLU GEMM at <= 320 rows
+GATEUP_KERNEL_SMALL_M = "gemm_mid_kernel<160, 192, 2, 2, 3, 3, 2, 0>"  # gate/up SwiGLU at 257-320 rows
 
 
 def log(*a):
@@ -494,7 +494,7 @@ def step_bench(wl, dr, ri, steps, warmup, graph=True, prof_steps=5):
     else:
         roof = {"bound": "mfma", "achieved": gf / g_avg_s / 1e12, "peak": peak_flops, "unit": "TFLOP/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    roof["kernel"] = GATEUP_KERNEL_SMALL_M if M <= 320 else "gemm_pipe_kernel (gate/up SwiGLU)"
+    roof["kernel"] = GATEUP_KERNEL_SMALL_M if M <= 320 else "gemm_large_kernel (gate/up SwiGLU)"
     roof["traffic"] = recorded_traffic(roof["kernel"]) if wl.name == "qwen3_8b_b1" else None
     roof["algorithmic_bytes_per_launch"] = gb
     roof["algorithmic_flops_per_launch"] = gf

@@ -114,7 +114,7 @@ int check_ctx(const dpara_ctx_t* x, int batch) {
 struct Plan {
   int B, R, Rp, M, S, chunk, CH, esz;
   int s_qkv, s_o, s_down;  // split-K planes of the QKV, O and down projections
-  bool afrag;              // normed activations in MFMA fragment order (QKV and gate/up GEMMs)
+  bool afrag;              // the attention norm's output in MFMA fragment order (QKV GEMM)
   bool qkv_fused;          // the QKV GEMM applies q/k-norm and RoPE in its epilogue
   int v_chunk, v_chunks, h_chunk, h_chunks;
   size_t X, A, QKV, Q, Kb, Vb, Opart, ML, O, Hmid, P, rope, vpart, G, Gsplit, logits, hpart, arpart, hcand, hwpart,
@@ -168,10 +168,8 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
   p.h_chunk = ar_head_chunk(c->dtype == DPARA_BF16 ? 1 : 0, c->ar_rank);
   p.h_chunks = (c->vocab + p.h_chunk - 1) / p.h_chunk;
   const int amode = c->dtype == DPARA_BF16 ? A_BF16 : A_F32;
-  // From 65 to 320 rows the GEMMs fed by an RMSNorm read their activations in fragment order
-  // (up to 64 rows the row-major LDS pipeline streams the weights faster: the 36-layer target
-  // at batch 1, 5.2-5.4 -> 4.8 ms).
-  p.afrag = c->dtype == DPARA_BF16 && p.M > 64 && p.M <= 320 && H % 256 == 0;
+  // From 193 to 320 rows the QKV GEMM reads its activations in fragment order.
+  p.afrag = c->dtype == DPARA_BF16 && p.M > 192 && p.M <= 320 && H % 256 == 0;
   // Above 320 rows the large-M kernel's epilogue applies q/k-norm and RoPE (128-wide heads; a
   // 256-column tile within one of W_q, W_k, W_v); otherwise split planes and the q/k-norm pass.
   const int kv_seg = nkv * hd;  // divides n_q heads' columns too
@@ -415,11 +413,7 @@ int run_decoder(const dpara_config_t* cfg, const dpara_layer_weights_t* layers, 
     }
     {
     Phase ph("rmsnorm", st);
-    if (p.afrag)
-      HIP_TRY(launch_rmsnorm_frag(M, H, X, P, p.s_o, (int64_t)M * H, Lw.mlp_norm, cfg->rms_eps, at<void>(ws, p.A), st),
-              "mlp_norm");
-    else
-      HIP_TRY(launch_rmsnorm(dt, M, H, X, M, 0, 0, P, p.s_o, (int64_t)M * H, 1, Lw.mlp_norm, cfg->rms_eps,
+    HIP_TRY(launch_rmsnorm(dt, M, H, X, M, 0, 0, P, p.s_o, (int64_t)M * H, 1, Lw.mlp_norm, cfg->rms_eps,
                              at<void>(ws, p.A), st),
               "mlp_norm");
     }
@@ -437,7 +431,7 @@ int run_decoder(const dpara_config_t* cfg, const dpara_layer_weights_t* layers, 
     gu.ldc = F;
     {
     Phase ph("gateup_gemm", st);
-    HIP_TRY(launch_gemm(p.afrag ? A_BF16_FRAG : amode, EPI_SWIGLU, gu, st), "gate/up gemm");
+    HIP_TRY(launch_gemm(amode, EPI_SWIGLU, gu, st), "gate/up gemm");
     }
     GemmArgs dn{};
     dn.A = at<void>(ws, p.Hmid);

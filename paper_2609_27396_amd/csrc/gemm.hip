@@ -1,11 +1,12 @@
 // Dense projections of the drafter: C[M, N] (op)= A[M, K] . B[N, K]^T.
 //
 // bf16 path: v_mfma_f32_16x16x32_bf16 kernels with fp32 accumulation and fused
-// epilogues (store fp32 or split-K fp32 planes, SwiGLU -> bf16, per-tile top-2 keys).
+// epilogues (store fp32 or split-K fp32 planes, SwiGLU -> bf16, per-tile top-2 keys).  Most
+// products over more than 64 rows go to gemm_large.hip; here are the others:
 // gemm_pipe_kernel streams both operands through a multi-stage direct-to-LDS ring; the LM
 // head's fp32 A operand arrives as two bf16 planes (hi + lo) that both meet every weight
-// tile.  gemm_adir_kernel (M <= 320) takes A in MFMA fragment order straight into registers
-// and only the weights through LDS.  Tile orders are XCD-aware: the tiles that share one
+// tile.  gemm_adir_kernel (Q|K|V at 193-320 rows) takes A in MFMA fragment order straight into
+// registers and only the weights through LDS.  Tile orders are XCD-aware: the tiles that share one
 // weight tile run on the same XCD back to back, so a weight tile is fetched from HBM once
 // and served to the others from that XCD's L2.
 // float32 path: a plain LDS-tiled FMA kernel for the float32 model configuration.
@@ -14,7 +15,6 @@
 
 namespace dpara {
 namespace {
-
 
 // silu(g) = g / (1 + e^-g) from the hardware exp2 and reciprocal (about 1 ulp each, far below
 // the bf16 rounding of the result; e^-g -> inf for very negative g gives g * 0 = -0).
@@ -337,7 +337,6 @@ __global__ __launch_bounds__(64 * WMW * WNW) void gemm_pipe_kernel(GemmArgs a, i
 }
 
 
-// ------------------------------------------------------------------ float32 FMA path
 // ------------------------------------------------------------ fragment-ordered A path
 // For M <= 320 one 320-row tile covers every row, so each workgroup multiplies the whole
 // activation operand with its own weight slice: A is re-read by every workgroup, the weights
@@ -346,9 +345,10 @@ __global__ __launch_bounds__(64 * WMW * WNW) void gemm_pipe_kernel(GemmArgs a, i
 // register ring SB stages deep (one 16-byte load per lane per 1 KB block).  Only the weight
 // tile (96 rows of B per 64-deep K step) goes through an LDS ring filled by direct DMA (as
 // non-temporal lines: each is read once) and read by all four waves.  Row blocks past the last valid one are clamped to it (their
-// accumulator rows are never stored).  SwiGLU tiles hold 48 gate + 48 up columns; the fp32
-// store splits K over `splits` workgroups writing planes [S][M][ldc].
-template <int EPI, int SB, int SKIP>
+// accumulator rows are never stored).  K is split over `splits` workgroups writing planes
+// [S][M][ldc].  Used for the Q|K|V projection at 193-320 rows (Qwen3-8B, 289 rows: 26 us; the
+// LDS pipeline 29); gate/up runs faster on the streaming kernels of gemm_large.hip.
+template <int SB, int SKIP>
 __global__ __launch_bounds__(256) void gemm_adir_kernel(GemmArgs a, int NT) {
   constexpr int BM = 320, BN = 96, BKB = 128, KB = 64, KS = KB / 32, CH = BKB / 16, RPI = 1024 / BKB;
   constexpr int NW = 4, WM = BM / NW, FM = WM / 16, FN = BN / 16;
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(256) void gemm_adir_kernel(GemmArgs a, int NT) {
   for (int j = 0; j < B_INS; ++j) {
     const int r = (wave + NW * j) * RPI + lrow;
     bool ok;
-    bsrc[j] = b_row<bf16_t, BN, EPI>(a, nt, r, ok) + kbeg + swz<CH>(r, lslot) * 8;
+    bsrc[j] = b_row<bf16_t, BN, EPI_STORE_F32>(a, nt, r, ok) + kbeg + swz<CH>(r, lslot) * 8;
   }
 
   bf16x8_t abuf[SB][KS][FM];
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(256) void gemm_adir_kernel(GemmArgs a, int NT) {
         bf16x8_t bfr[FN];
 #pragma unroll
         for (int ni = 0; ni < FN; ++ni) {
-          const int r = b_frag_row<BN, BN, FN, EPI>(0, ni) + lr;
+          const int r = ni * 16 + lr;
           bfr[ni] = *(const bf16x8_t*)(sb + r * BKB + swz<CH>(r, c) * 16);
         }
 #pragma unroll
@@ -441,24 +441,6 @@ __global__ __launch_bounds__(256) void gemm_adir_kernel(GemmArgs a, int NT) {
   }
   wait_vmcnt<0>();
 
-  if constexpr (EPI == EPI_SWIGLU) {
-    constexpr int OC = BN / 2, LDO = OC + 8;
-    static_assert(BM * LDO * 2 <= SB * STAGE_BYTES, "the output tile fits the ring");
-    bf16_t* so = (bf16_t*)smem;
-    __syncthreads();  // every wave is done with the ring
-#pragma unroll
-    for (int mi = 0; mi < FM; ++mi)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int lrow = wave * WM + mi * 16 + lc * 4 + r;
-#pragma unroll
-        for (int ni = 0; ni < FN / 2; ++ni)
-          so[lrow * LDO + ni * 16 + lr] = f2bf(silu_f(acc[mi][ni][r]) * acc[mi][ni + FN / 2][r]);
-      }
-    __syncthreads();
-    swiglu_copy_out<BM, OC, LDO>(so, (bf16_t*)a.C, a.ldc, 0, nt * OC, a.M, a.N);
-    return;
-  }
 #pragma unroll
   for (int mi = 0; mi < FM; ++mi) {
 #pragma unroll
@@ -548,21 +530,17 @@ hipError_t run_f32(const GemmArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int EPI>
 hipError_t run_adir(const GemmArgs& a, hipStream_t st) {
   constexpr int SB = 4, BN = 96, lds = SB * BN * 128;
-  static_assert(EPI == EPI_SWIGLU || EPI == EPI_STORE_F32, "fragment-ordered A: SwiGLU or fp32 store");
   if (a.M > 320 || a.K % 32) return hipErrorInvalidValue;
-  if (a.splits < 1 || (a.splits > 1 && EPI != EPI_STORE_F32) || a.K % (a.splits * 64 * SB) != 0)
-    return hipErrorInvalidValue;
-  const int NT = EPI == EPI_SWIGLU ? (a.N + BN / 2 - 1) / (BN / 2) : (a.N + BN - 1) / BN;
-  // Up to 240 rows at least the last wave's 80 rows are empty: skip the products of row blocks
-  // past M (the 36-layer target verifying 17 rows a request: 5.75 -> 5.40 ms at batch 1).
-  auto kern = a.M <= 240 ? gemm_adir_kernel<EPI, SB, 1> : gemm_adir_kernel<EPI, SB, 0>;
+  if (a.splits < 1 || a.K % (a.splits * 64 * SB) != 0) return hipErrorInvalidValue;
+  const int NT = (a.N + BN - 1) / BN;
+  // Up to 240 rows the last wave's 80 rows are empty: skip the products of row blocks past M.
+  auto kern = a.M <= 240 ? gemm_adir_kernel<SB, 1> : gemm_adir_kernel<SB, 0>;
   static const hipError_t attr0 =
-      hipFuncSetAttribute((const void*)gemm_adir_kernel<EPI, SB, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      hipFuncSetAttribute((const void*)gemm_adir_kernel<SB, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   static const hipError_t attr1 =
-      hipFuncSetAttribute((const void*)gemm_adir_kernel<EPI, SB, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      hipFuncSetAttribute((const void*)gemm_adir_kernel<SB, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (attr0 != hipSuccess) return attr0;
   if (attr1 != hipSuccess) return attr1;
   hipLaunchKernelGGL(kern, dim3(NT * a.splits), dim3(256), lds, st, a, NT);
@@ -587,15 +565,14 @@ hipError_t run_pipe(const GemmArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Tile choice for the bf16 projections of at most 320 rows (measured on MI355X at Qwen3-8B N/K):
-//  65-320   : weight streaming.  One 320-row tile covers every row, so each weight tile is
-//             read once; 8 waves (80x64 each), a 2-deep ring of 64-wide K steps (SwiGLU:
-//             320x96 tiles of 4 waves, 80 x (48 gate + 48 up) each).  The
-//             fp32-store GEMMs (QKV, O, down, append) split K so that about 256 workgroups
-//             run; their consumers add the S partial planes (gemm_splits).
+// Tile choice for the bf16 projections that gemm_mid_supported() and gemm_large_supported() leave
+// (measured on MI355X at Qwen3-8B N/K):
 //  M <= 64  : (the context append, up to gamma+1 rows per request) 64x128 tiles, 3-deep ring.
-// More rows come here only when gemm_large_supported() says no (K not a multiple of 128): the
-// 64-row tiles take any shape.
+//  65-320   : O and down above 192 rows, and any K that is no multiple of 128: one 320-row tile
+//             covers every row, so each weight tile is read once; 8 waves (80x64 each), a 2-deep
+//             ring of 64-wide K steps.  The fp32-store GEMMs split K so that about 256 workgroups
+//             run; their consumers add the S partial planes (gemm_splits).
+//  above    : a K that is no multiple of 128: 64-row tiles.
 template <int EPI>
 hipError_t run_bf16(const GemmArgs& a, hipStream_t st) {
   // up to 32 rows (a 17-row verification, the context append, the sampled head's scores): a
@@ -609,7 +586,7 @@ hipError_t run_bf16(const GemmArgs& a, hipStream_t st) {
   // the whole target with the 128-deep stages.
   if constexpr (EPI == EPI_SWIGLU)
     if (a.M <= 64) return run_pipe<64, 96, 4, 1, 3, 256, EPI>(a, st);
-  // SwiGLU: 48 gate + 48 up rows per tile, so that the Qwen3-8B FFN (12288) gives 256 tiles
+  // SwiGLU: 48 gate + 48 up rows per tile
   if constexpr (EPI == EPI_SWIGLU) return run_pipe<320, 96, 4, 1, 2, 128, EPI>(a, st);
   return run_pipe<320, 128, 4, 2, 2, 128, EPI>(a, st);
 }
@@ -626,6 +603,7 @@ int gemm_splits(int amode, int epi, int M, int N, int K, int seg) {
     return S;
   }
   if (amode != A_BF16 || epi != EPI_STORE_F32) return 1;
+  if (M > 64 && M <= 192 && N <= 32768 && K % 128 == 0 && K >= 256 && seg % 128 == 0) return gemm_mid_splits(N, K);
   if (M > 320) return K % 128 == 0 && K >= 256 && seg % 256 == 0 ? gemm_large_splits(M, N, K) : 1;
   const int NT = (N + 127) / 128;
   const int max_wg = M <= 64 ? 512 : 256;  // the M <= 64 tile fits two workgroups per CU
@@ -665,28 +643,21 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st) {
     if (a.M > 128 && a.M <= 256) return run_pipe<256, 128, 4, 2, 2, 128, EPI_STORE_F32, 1>(a, st);
     return run_pipe<128, 128, 4, 2, 3, 128, EPI_STORE_F32, 1>(a, st);
   }
+  if (amode == A_BF16 && epi == EPI_TOP2 && a.ldc < (a.N + 127) / 128) return hipErrorInvalidValue;
+  if (amode == A_BF16 && gemm_mid_supported(epi, a)) return launch_gemm_mid(epi, a, st);
   if (amode == A_BF16 && gemm_large_supported(epi, a)) {
-    if (epi == EPI_TOP2 && a.ldc < (a.N + 127) / 128) return hipErrorInvalidValue;
     if (epi == EPI_QKV && (a.N != (a.qkv.n_q + 2 * a.qkv.n_kv) * 128 || a.qkv.n_kv < 1 || a.qkv.n_q % a.qkv.n_kv ||
                            a.qkv.R < 1 || a.qkv.Rp < a.qkv.R))
       return hipErrorInvalidValue;
     return launch_gemm_large(epi, a, st);
   }
-  if (epi == EPI_TOP2) {
-    // Top-2 over at most 320 rows from one bf16 plane, measured on MI355X at the Qwen3
-    // vocabulary: 192 x 128 tiles (4 waves of 96 x 64, a 2-deep ring of 80 KB), 22% faster at
-    // 272 rows than 256 x 256; exactly 193-256 rows (the greedy head's ranking at batch 13-16)
-    // take one 256 x 256 tile row (the batch-16 head 587 -> 526 us against two 192-row tiles).
-    // (More rows only with a K that is no multiple of 128.)
+  if (epi == EPI_TOP2) {  // at most 64 rows, or a K that is no multiple of 128
     if (amode != A_BF16 || a.ldc < (a.N + 127) / 128) return hipErrorInvalidValue;
-    if (a.M > 192 && a.M <= 256) return run_pipe<256, 256, 2, 4, 2, 128, EPI_TOP2, 0>(a, st);
     return run_pipe<192, 128, 2, 2, 2, 128, EPI_TOP2, 0>(a, st);
   }
   if (epi == EPI_QKV) return hipErrorInvalidValue;  // the large-M kernel's epilogue
   if (amode == A_BF16_FRAG) {
-    if (epi == EPI_SWIGLU) return run_adir<EPI_SWIGLU>(a, st);
-    if (epi == EPI_STORE_F32) return run_adir<EPI_STORE_F32>(a, st);
-    return hipErrorInvalidValue;
+    return epi == EPI_STORE_F32 ? run_adir(a, st) : hipErrorInvalidValue;
   }
   if (amode != A_BF16) return hipErrorInvalidValue;
   switch (epi) {

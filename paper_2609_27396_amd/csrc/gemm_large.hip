@@ -1,5 +1,6 @@
-// bf16 projections over more than 320 rows: a persistent, software-pipelined GEMM.
+// bf16 projections over more than 64 rows: persistent, software-pipelined GEMMs.
 //
+// More than 320 rows (gemm_large_kernel).
 // What bounds a 256 x 256 tile on a CU, per 64-deep K step: the MFMAs (0.98 us at the clock the
 // chip holds), the LDS-DMA of its 64 KB of operands (0.97 us from L2 / Infinity Cache at the
 // rate 256 CUs reach together) and 192 KB of LDS fragment reads (0.42 us).  The three must run
@@ -88,7 +89,7 @@ __device__ __forceinline__ void large_tile(int t, int total, int MT, int NT, int
 // without spilling.
 template <int FM, int FN>
 struct HalfPlan {
-  static constexpr int GRP = FM * FN % 4 == 0 ? 4 : 2, NG = FM * FN / GRP, LO = FM / 2, HI = FM - LO;
+  static constexpr int GRP = FM * FN % 4 == 0 && FM * FN >= 8 ? 4 : 2, NG = FM * FN / GRP, LO = FM / 2, HI = FM - LO;
   static_assert(FM * FN % GRP == 0 && NG >= 2, "whole groups of MFMAs");
   static constexpr int mi(int t) { return t < LO * FN ? t % LO1 : LO + (t - LO * FN) % HI; }
   static constexpr int ni(int t) { return t < LO * FN ? t / LO1 : (t - LO * FN) / HI; }
@@ -113,10 +114,10 @@ struct HalfPlan {
 
 // Epilogue of one BM x BN tile whose wave (wm, wn) holds rows m0 + wm * WM .. and columns
 // wn * WN .. of column tile nt: lane (lr, lc) has row .. + mi * 16 + lr and the four columns
-// ni * 16 + lc * 4 .. of every fragment (mi, ni).  stg: kStageWave bytes of LDS of this wave alone.
+// ni * 16 + lc * 4 .. of every fragment (mi, ni); rows from m_end on are not the tile's.  stg: kStageWave bytes of LDS of this wave alone.
 template <int BN, int WM, int WN, int WNW, int EPI>
 __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)[WM / 16][WN / 16], int s, int row0,
-                                               int nt, int wn, int lane, bf16_t* stg) {
+                                               int m_end, int nt, int wn, int lane, bf16_t* stg) {
   constexpr int FM = WM / 16, FN = WN / 16;
   const int lr = lane & 15, lc = lane >> 4;
   const int row_w = row0 + lr;
@@ -134,7 +135,7 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
 #pragma unroll
       for (int mi = 0; mi < FM; ++mi) {
         __builtin_amdgcn_sched_barrier(0);
-        const int row = row_w + mi * 16, rc = min(row, a.M - 1), b = rc / e.R, rr = rc - b * e.R;
+        const int row = row_w + mi * 16, rc = min(row, m_end - 1), b = rc / e.R, rr = rc - b * e.R;
         if (e.qk_norm) {
           float ss = 0.f;
 #pragma unroll
@@ -167,7 +168,7 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
             lo[r] = l * co[r] + -1.f * h * si[r];
             hi[r] = h * co[r] + 1.f * l * si[r];
           }
-          if (row < a.M) {
+          if (row < m_end) {
             *(uint2*)(dst + ni * 16) = pack4(lo[0], lo[1], lo[2], lo[3]);
             *(uint2*)(dst + ni * 16 + 64) = pack4(hi[0], hi[1], hi[2], hi[3]);
           }
@@ -176,7 +177,7 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
     } else {
       // V^T [128][Rp] per request: 16 columns at a time through this wave's LDS, so that a store
       // covers the wave's consecutive rows of one head dimension
-      const int row = row0 + lane, rc = min(row, a.M - 1), b = rc / e.R;
+      const int row = row0 + lane, rc = min(row, m_end - 1), b = rc / e.R;
       bf16_t* dst = (bf16_t*)e.Vb + (int64_t)(b * e.n_kv + (slot - e.n_q - e.n_kv)) * 128 * e.Rp + (rc - b * e.R);
 #pragma unroll
       for (int ni = 0; ni < FN; ++ni) {
@@ -185,7 +186,7 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
         for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
           for (int r = 0; r < 4; ++r) stg[(lc * 4 + r) * 64 + mi * 16 + lr] = f2bf(acc[mi][ni][r]);
-        if (lane < WM && row < a.M)
+        if (lane < WM && row < m_end)
 #pragma unroll 8
           for (int d = 0; d < 16; ++d) dst[(int64_t)(ni * 16 + d) * e.Rp] = stg[d * 64 + lane];
       }
@@ -217,7 +218,7 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
         u.v3 = __shfl_xor(t.v3, o, 64);
         t = Top3::merge(t, u);
       }
-      if (lc == 0 && row < a.M && tile < n_tiles) {
+      if (lc == 0 && row < m_end && tile < n_tiles) {
         uint64_t* o = (uint64_t*)a.C + ((int64_t)row * a.ldc + tile) * 3;
         o[0] = t.k1;
         o[1] = t.k2;
@@ -225,7 +226,7 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
       }
       continue;
     }
-    if (row >= a.M) continue;
+    if (row >= m_end) continue;
     if constexpr (EPI == EPI_SWIGLU) {
       const int f0 = nt * (BN / 2) + wn * (WN / 2) + lc * 4;
       bf16_t* c = (bf16_t*)a.C + (int64_t)row * a.ldc + f0;
@@ -267,27 +268,28 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
   }
 }
 
-// A list of n tiles of BM rows (item(i): K split s, first row m0, column tile nt), 8 waves as
-// WMW x WNW; BM and BN multiples of 64, K a multiple of 128, at least
-// 256 per split.
-template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, typename Item>
-__device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item& item, unsigned char* smem) {
+// A list of n tiles of `rows` <= BM rows (item(i): K split s, first row m0, column tile nt) for
+// WMW x WNW waves; K a multiple of 128, at least 256 per split.  NA, NB: ring slots of A and B;
+// STREAM: the weights are read once, as non-temporal lines (the activations stay in L2).
+template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, int STREAM, typename Item>
+__device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, int rows, const Item& item, unsigned char* smem) {
   constexpr int NW = WMW * WNW, WM = BM / WMW, WN = BN / WNW, FM = WM / 16, FN = WN / 16;
-  constexpr int AI = BM / 64, BI = BN / 64, ND = AI + BI;  // 1 KB DMA instructions per wave and K step
+  constexpr int GR = 8 * NW;  // tile rows one DMA instruction of every wave loads
+  constexpr int AI = BM / GR, BI = BN / GR, ND = AI + BI;  // 1 KB DMA instructions per wave and K step
   constexpr int A_SLOT = BM * 128, B_SLOT = BN * 128, B0 = NA * A_SLOT, RING = NA * A_SLOT + NB * B_SLOT;
   // loads a step's barrier may leave in flight: those issued after the next step's (vmcnt counts
   // in order)
   static_assert(NA == NB || (NA == 2 && NB == 3), "ring depths");
   constexpr int LATER = NA == NB ? (NB - 2) * ND : BI;
   using P = HalfPlan<FM, FN>;
-  static_assert(NW == 8, "8 waves");
+  static_assert(BM % GR == 0 && BN % GR == 0, "whole DMA groups");
   static_assert(EPI != EPI_SWIGLU || FN % 2 == 0, "gate and up fragments in pairs");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WNW, wn = wave % WNW;
   const int lr = lane & 15, lc = lane >> 4;
 
-  // DMA sources.  One instruction of a wave loads 8 rows of 128 bytes; the eight waves' q-th
-  // loads cover rows 64 q .. of the tile's A or B rows (the same byte offsets for both: lda == K).
+  // DMA sources.  One instruction of a wave loads 8 rows of 128 bytes; the waves' q-th
+  // loads cover rows GR q .. of the tile's A or B rows (the same byte offsets for both: lda == K).
   // Rows past M or N lie outside the buffer descriptor: nothing is read for them, and what their
   // LDS rows hold only reaches rows and columns the epilogue does not store.  A row's 16-byte
   // chunk c sits in LDS slot c ^ (row % 8), so fragment reads (16 rows, one chunk) spread over
@@ -295,10 +297,12 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
   const int K2 = a.K * 2;
   const int lrow = lane >> 3;
   constexpr int BP = EPI == EPI_SWIGLU ? 2 : 1;  // B parts: gate and up rows
-  int voff[AI > BI / BP ? AI : BI / BP];
+  constexpr int BG = BI / BP;  // groups of a part
+  static_assert(BG * BP == BI, "whole groups of a part");
+  int voff[AI > BG ? AI : BG];
 #pragma unroll
-  for (int q = 0; q < (AI > BI / BP ? AI : BI / BP); ++q)
-    voff[q] = (q * 64 + wave * 8 + lrow) * K2 + (((lane & 7) ^ lrow) * 16);
+  for (int q = 0; q < (AI > BG ? AI : BG); ++q)
+    voff[q] = (q * GR + wave * 8 + lrow) * K2 + (((lane & 7) ^ lrow) * 16);
   const char *pa, *pb[BP];  // the tile the next A load and the next B load belong to
   unsigned na, nb;          // valid bytes from there
   int ka = 0, kb = 0;       // and their K steps within it
@@ -306,7 +310,7 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
   auto k_byte = [&](int s) { return (int)((int64_t)(a.K / 128) * s / a.splits) * 256; };
   auto a_source = [&](int s, int m0, const char*& p, unsigned& n) {
     p = (const char*)a.A + (int64_t)m0 * K2 + k_byte(s);
-    n = (unsigned)(min(BM, a.M - m0) * K2 - k_byte(s));
+    n = (unsigned)(min(rows, a.M - m0) * K2 - k_byte(s));
   };
   auto b_source = [&](int s, int nt, const char* (&p)[BP], unsigned& n) {
     const int c = nt * (BN / BP), left = min(BN / BP, a.N - c);
@@ -332,11 +336,15 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
   // q-th load of A step ka into A slot `as`, or of B step kb into B slot `bs`
   auto dma = [&](int q, int as, int bs) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    const int j = q < AI ? q : q - AI, part = q < AI ? 0 : j / (BI / BP);
-    const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)(q < AI ? pa : pb[part]), 0, (int)(q < AI ? na : nb), 0x00020000);
-    unsigned char* dst = smem + (q < AI ? as * A_SLOT : B0 + bs * B_SLOT) + (wave + NW * j) * 1024;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)dst, 16, voff[q < AI ? q : j % (BI / BP)],
-                                             (q < AI ? ka : kb) * 128, 0, 0);
+    unsigned char* dst = smem + (q < AI ? as * A_SLOT : B0 + bs * B_SLOT) + (wave + NW * (q < AI ? q : q - AI)) * 1024;
+    if (q < AI) {
+      const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)pa, 0, (int)na, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)dst, 16, voff[q], ka * 128, 0, 0);
+    } else {
+      const int j = q - AI;
+      const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)pb[j / BG], 0, (int)nb, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)dst, 16, voff[j % BG], kb * 128, 0, STREAM ? 2 : 0);
+    }
 #endif
   };
 
@@ -457,7 +465,7 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, const Item
     // (the next tile's first fragments are read again after the epilogue: 48 registers less
     // while it runs)
     __builtin_amdgcn_sched_barrier(0);
-    large_epilogue<BN, WM, WN, WNW, EPI>(a, acc, s, m0 + wm * WM, nt, wn, lane, (bf16_t*)(smem + RING + wave * kStageWave));
+    large_epilogue<BN, WM, WN, WNW, EPI>(a, acc, s, m0 + wm * WM, min(a.M, m0 + rows), nt, wn, lane, (bf16_t*)(smem + RING + wave * kStageWave));
     __builtin_amdgcn_sched_barrier(0);
     s = s1;
     m0 = m1;
@@ -476,7 +484,7 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs a, LargePla
   // full tiles w, w + grid, ..; then this workgroup's share of the tails
   const int n_full = w < p.full ? (p.full - w + p.grid - 1) / p.grid : 0;
   if (n_full > 0)
-    large_tiles<BM, BN, 4, 2, 2, NB, EPI>(a, n_full, [&](int i, int& s, int& m0, int& nt) {
+    large_tiles<BM, BN, 4, 2, 2, NB, EPI, 0>(a, n_full, BM, [&](int i, int& s, int& m0, int& nt) {
       int mt;
       large_tile(w + p.grid * i, p.full, p.mtf, p.NT, s, mt, nt);
       m0 = mt * BM;
@@ -491,14 +499,32 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs a, LargePla
     constexpr int TD = tail_depth(EPI, TAIL);
     // 64 rows: 2 x 4 waves where 64 columns a wave will do (a third fewer LDS reads)
     constexpr int WNW = TAIL == 64 && BN == 256 && EPI != EPI_QKV && EPI != EPI_TOP2 ? 4 : 2;
-    large_tiles<TAIL, BN, 8 / WNW, WNW, TD, TD, EPI>(
-        a, n1 + n2, [&](int i, int& s, int& m0, int& nt) {
+    large_tiles<TAIL, BN, 8 / WNW, WNW, TD, TD, EPI, 0>(
+        a, n1 + n2, TAIL, [&](int i, int& s, int& m0, int& nt) {
           const int t = i < n1 ? fr + p.nfree * i : p.tails1 + w + p.grid * (i - n1);
           s = t / p.NT;
           nt = t - s * p.NT;
           m0 = p.mtf * BM;
         }, smem);
   }
+}
+
+// 65 to 320 rows: weight streaming.  One or a few row tiles of equal height cover the rows, so the
+// weights are read once from HBM; workgroups walk the tiles as above, one or two to a CU.
+template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, int STREAM>
+__global__ __launch_bounds__(64 * WMW * WNW, (NA * BM + NB * BN) * 128 <= 81920 ? WMW * WNW / 2 : WMW * WNW / 4) void
+gemm_mid_kernel(GemmArgs a, int MT, int NT, int rows) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if (a.only_if && *a.only_if == 0) return;
+  debug_poison_lds<(NA * BM + NB * BN) * 128>(smem);
+  const int w = blockIdx.x, grid = gridDim.x, total = MT * NT * a.splits;
+  large_tiles<BM, BN, WMW, WNW, NA, NB, EPI, STREAM>(a, (total - w + grid - 1) / grid, rows,
+                                                     [&](int i, int& s, int& m0, int& nt) {
+                                                       int mt;
+                                                       large_tile(w + grid * i, total, MT, NT, s, mt, nt);
+                                                       m0 = mt * rows;
+                                                     },
+                                                     smem);
 }
 
 constexpr int kCus = 256;
@@ -594,7 +620,91 @@ hipError_t pick_large(const GemmArgs& a, hipStream_t st) {
   return run_large<256, 256, EPI>(a, st);
 }
 
+template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, int STREAM>
+hipError_t run_mid(const GemmArgs& a, hipStream_t st) {
+  constexpr int lds = (NA * BM + NB * BN) * 128;
+  static_assert(lds <= 163840, "LDS");
+  auto kern = gemm_mid_kernel<BM, BN, WMW, WNW, NA, NB, EPI, STREAM>;
+  static const hipError_t attr =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (attr != hipSuccess) return attr;
+  constexpr int COLS = EPI == EPI_SWIGLU ? BN / 2 : BN, slots = lds <= 81920 ? 2 * kCus : kCus;
+  const int MT = (a.M + BM - 1) / BM, NT = (a.N + COLS - 1) / COLS, T = MT * NT * a.splits;
+  hipLaunchKernelGGL(kern, dim3(T < slots ? T : slots), dim3(64 * WMW * WNW), lds, st, a, MT, NT,
+                     (a.M + MT - 1) / MT);
+  return hipGetLastError();
+}
+
+// Tiles for 65 to 320 rows, measured on MI355X at Qwen3-8B widths with the weights in HBM (us, and
+// what the kernels used before took):
+//  SwiGLU   : up to 128 rows 128 x 128 (192 workgroups at Qwen3-8B; 128 x 192 where that takes
+//             fewer rounds): 102 rows 46 (63), Qwen3-14B 73.  Above, two equal row tiles x 192
+//             columns by four waves, so that Qwen3-8B gives 256 workgroups and the two that share
+//             a weight tile read it from one XCD's L2: 170 rows 54 (65), 238 59 (66), 289 63 (70).
+//  fp32     : up to 192 rows one row tile x 128 columns, K split over up to 256 workgroups: 102 rows
+//             down 25 (36), O 13 (17), Q|K|V 18 (24); 170 rows down 30, O 16, Q|K|V 21.
+//  LM head  : wide tiles, so that the last round is nearly full: 102 rows x 320 columns 228 (371),
+//             170 x 256 267, 238 x 192 340, 272 rows as two row tiles of 160 x 256 373 (382).
+//  top-2    : 128-column wave tiles: 128, 192, 256 (or two of 160) rows x 256 columns.
+template <int EPI>
+hipError_t pick_mid(const GemmArgs& a, hipStream_t st) {
+  if constexpr (EPI == EPI_SWIGLU) {
+    if (a.M <= 128) {  // a K step's loads: the rows and the columns of the tile
+      const int r128 = ((a.N + 63) / 64 + kCus - 1) / kCus, r192 = ((a.N + 95) / 96 + kCus - 1) / kCus;
+      if (r128 * (a.M + 128) <= r192 * (a.M + 192)) return run_mid<128, 128, 4, 2, 3, 3, EPI, 1>(a, st);
+      return run_mid<128, 192, 2, 2, 3, 3, EPI, 1>(a, st);
+    }
+    if (a.M <= 192) return run_mid<96, 192, 2, 2, 3, 3, EPI, 0>(a, st);
+    if (a.M <= 256) return run_mid<128, 192, 2, 2, 3, 3, EPI, 0>(a, st);
+    return run_mid<160, 192, 2, 2, 3, 3, EPI, 0>(a, st);
+  } else if constexpr (EPI == EPI_TOP2) {
+    if (a.M <= 128) return run_mid<128, 256, 4, 2, 2, 3, EPI, 1>(a, st);
+    if (a.M <= 192) return run_mid<192, 256, 4, 2, 2, 3, EPI, 1>(a, st);
+    if (a.M <= 256) return run_mid<256, 256, 4, 2, 2, 3, EPI, 1>(a, st);
+    return run_mid<160, 256, 2, 2, 2, 3, EPI, 0>(a, st);
+  } else {
+    if (a.N > 32768) {  // (S == 1: a vocabulary's columns)
+      if (a.M <= 128) return run_mid<128, 320, 4, 2, 2, 3, EPI, 1>(a, st);
+      if (a.M <= 192) return run_mid<192, 256, 4, 2, 2, 3, EPI, 1>(a, st);
+      if (a.M <= 256) return run_mid<256, 192, 4, 2, 2, 3, EPI, 1>(a, st);
+      return run_mid<160, 256, 2, 2, 2, 3, EPI, 0>(a, st);
+    }
+    if (a.M <= 128) return run_mid<128, 128, 4, 2, 3, 3, EPI, 1>(a, st);
+    return run_mid<192, 128, 4, 2, 3, 3, EPI, 1>(a, st);
+  }
+}
+
 }  // namespace
+
+bool gemm_mid_supported(int epi, const GemmArgs& a) {
+  if (a.M <= 64 || a.M > 320 || a.splits < 1 || a.K % 128 != 0 || a.K / 128 < 2 * a.splits || a.lda != a.K) return false;
+  if (a.splits > 1 && epi != EPI_STORE_F32) return false;
+  if (epi == EPI_SWIGLU) return a.N % 8 == 0 && a.ldc % 4 == 0;
+  if (epi == EPI_TOP2) return a.seg_rows == 0 && a.n1 >= a.N;
+  if (epi != EPI_STORE_F32 && epi != EPI_STORE_BF16) return false;
+  if (a.N > 32768) return a.splits == 1 && a.seg_rows == 0 && a.n1 >= a.N;
+  // a 128-column tile comes from one weight segment
+  const bool segs = a.seg_rows > 0 ? a.seg_rows % 128 == 0
+                                   : (a.n1 >= a.N || a.n1 % 128 == 0) && (a.n2 >= a.N || a.n2 % 128 == 0);
+  return a.M <= 192 && segs;
+}
+
+int gemm_mid_splits(int N, int K) {
+  int S = kCus / ((N + 127) / 128);
+  if (S > 8) S = 8;  // the consumers' plane reads grow with S
+  if (S > K / 256) S = K / 256;
+  return S < 1 ? 1 : S;
+}
+
+hipError_t launch_gemm_mid(int epi, const GemmArgs& a, hipStream_t st) {
+  if (!gemm_mid_supported(epi, a)) return hipErrorInvalidValue;
+  switch (epi) {
+    case EPI_SWIGLU: return pick_mid<EPI_SWIGLU>(a, st);
+    case EPI_STORE_F32: return pick_mid<EPI_STORE_F32>(a, st);
+    case EPI_STORE_BF16: return pick_mid<EPI_STORE_BF16>(a, st);
+    default: return pick_mid<EPI_TOP2>(a, st);
+  }
+}
 
 bool gemm_large_supported(int epi, const GemmArgs& a) {
   if (a.M <= 320 || a.splits < 1 || a.K % 128 != 0 || a.K / 128 < 2 * a.splits || a.lda != a.K) return false;

@@ -43,7 +43,7 @@ struct QkvEpi {
 // A_BF16_DUAL: A given as two bf16 planes hi (at A) and lo (at A + lo_off elements) with
 // hi + lo = the float32 operand to ~16 significant bits; both planes meet every weight tile.
 // A_BF16_FRAG: A is bf16 in MFMA fragment order (frag_index; lda unused), M <= 320,
-// K a multiple of 256 * splits; EPI_SWIGLU or EPI_STORE_F32 only.
+// K a multiple of 256 * splits; EPI_STORE_F32 only.
 enum GemmAMode { A_BF16 = 0, A_BF16_FRAG = 1, A_F32 = 2, A_BF16_DUAL = 3 };
 
 // Element (row, k) of a bf16 operand stored in MFMA fragment blocks: blocks of 16 rows x 32 k
@@ -81,6 +81,11 @@ struct GemmArgs {
 
 constexpr int kMaxGemmSegs = 16;
 hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st);
+// The streaming kernels for 65 to 320 bf16 rows (gemm_large.hip): whether they take this call,
+// its launch, and the split-K planes of its float32 store (at most 192 rows).
+bool gemm_mid_supported(int epi, const GemmArgs& a);
+hipError_t launch_gemm_mid(int epi, const GemmArgs& a, hipStream_t st);
+int gemm_mid_splits(int N, int K);
 // The persistent kernel for more than 320 bf16 rows (gemm_large.hip): whether it takes this
 // call, and its launch.
 bool gemm_large_supported(int epi, const GemmArgs& a);

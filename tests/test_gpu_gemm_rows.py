@@ -1,0 +1,109 @@
+"""The bf16 projections at the row counts where another tile takes over, and with shapes whose
+column tiles, K splits and row tails are ragged, against the CPU oracle."""
+import sys
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import dpara_oracle as O  # noqa: E402
+from paper_2609_27396_amd import synth  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-2  # the bf16 bar of test_gpu_parity
+# K of a fusion is 3 * hidden: 384 (three 128-deep steps) and 960 (no multiple of 128)
+ROWS = [64, 65, 128, 129, 192, 193, 320, 321, 385, 513]
+
+
+def _say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+def _shape(hidden, ffn, vocab, gamma, layers=1):
+    return synth.DrafterShape(n_layers=layers, hidden=hidden, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn=ffn,
+                              vocab=vocab, gamma=gamma, ar_rank=64, qk_norm=True, dtype="bf16")
+
+
+@pytest.mark.parametrize("hidden", [128, 320])
+def test_fused_features_around_tile_edges(hidden):
+    from paper_2609_27396_amd import dpara as D
+    s = _shape(hidden, 256, 500, 4)
+    wf = synth.make_fusion_weights(s, n_feat=3, seed=21, gain_jitter=0.1)
+    fus = D.DeviceFusion(s, wf, 3)
+    for n in ROWS:
+        _say("case fuse", hidden, n)
+        hid = synth.make_target_hidden(s, n, n_feat=3, seed=22 + n)
+        out = torch.empty((n, hidden), dtype=torch.bfloat16, device="cuda")
+        ws = torch.empty(D.dpara_fuse_workspace_bytes(fus.cfg, n, 3), dtype=torch.uint8, device="cuda")
+        D.fuse_features(fus, torch.from_numpy(hid).to(device="cuda", dtype=torch.bfloat16), out, ws)
+        torch.cuda.synchronize()
+        ref = O.fuse_features(s, wf, hid, "bf16")
+        # one bf16 rounding, and the float32 summation error of a 3H-term projection near zero
+        assert np.all(np.abs(out.float().cpu().numpy() - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-4), n
+
+
+# requests of 17 block rows: 68, 119 | 136, 187 | 204, 255 | 272, 306 | 323, 391 rows.  hidden 384 is
+# three 128-deep K steps; ffn 640 and vocab 3001 leave ragged column tiles at every tile width
+@pytest.mark.parametrize("batch", [4, 7, 8, 11, 12, 15, 16, 18, 19, 23])
+def test_target_rows_around_tile_edges(batch):
+    from paper_2609_27396_amd import dpara as D
+    from paper_2609_27396_amd.harness import upload_cache
+    s = _shape(384, 640, 3001, 16, layers=2)
+    lens = [(29 * i) % 70 for i in range(batch)]
+    _say("case target rows", batch * 17)
+    w = synth.make_target_weights(s, seed=7, gain_jitter=0.1)
+    k, v = synth.make_target_cache(s, lens, seed=8)
+    block = np.random.default_rng(batch).integers(0, s.vocab, (batch, 17)).astype(np.int32)
+    t = D.DeviceTarget(s, w)
+    ctx = D.DeviceContext(s, batch, 128)
+    upload_cache(ctx, k, v, lens, torch.bfloat16)
+    ws = D.Workspace(t.cfg, batch, 128, target=True)
+    lf = torch.empty((batch, 17, s.vocab), dtype=torch.float32, device="cuda")
+    lb = torch.empty_like(lf, dtype=torch.bfloat16)
+    D.target_forward(t, ctx, torch.from_numpy(block).cuda(), lf, ws)
+    D.target_forward(t, ctx, torch.from_numpy(block).cuda(), lb, ws)
+    torch.cuda.synchronize()
+    for b in sorted({0, batch // 2, batch - 1}):
+        ref = O.target_forward(s, w, [k[l][b] for l in range(2)], [v[l][b] for l in range(2)], block[b], "bf16")
+        assert np.abs(lf[b].cpu().numpy() - ref).max() <= TOL, b
+    # bf16 logits are the float32 logits rounded once
+    np.testing.assert_allclose(lb.float().cpu().numpy(), lf.cpu().numpy(), rtol=2 ** -8, atol=0)
+
+
+# branch rows batch * (gamma + 1) * gamma: 72, 126 | 144, 180 | 198, 252 | 270, 320 | 360
+@pytest.mark.parametrize("batch,gamma", [(6, 3), (3, 6), (2, 8), (9, 4), (1, 13), (6, 6), (3, 9), (16, 4), (4, 9)])
+def test_candidate_rows_around_tile_edges(batch, gamma):
+    """Candidates of every branch row, then the serial step: where every step is proven, bit for
+    bit the plain head (whose rows are at most 64 here and take another kernel)."""
+    from paper_2609_27396_amd import dpara as D
+    s = _shape(256, 256, 3000, gamma)
+    _say("case candidate rows", batch * (gamma + 1) * gamma)
+    w = synth.make_weights(s, seed=6, gain_jitter=0.1, ar_w_std=0.005, ar_e_std=0.02)
+    dd = D.DeviceDrafter(s, w)
+    ws = D.Workspace(dd.cfg, batch, 64)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(batch)
+    reps = torch.empty((batch, gamma + 1, gamma, s.hidden), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    rng = np.random.default_rng(gamma)
+    acc = torch.from_numpy(rng.integers(0, gamma + 1, batch).astype(np.int32)).cuda()
+    bon = torch.from_numpy(rng.integers(0, s.vocab, batch).astype(np.int32)).cuda()
+
+    def outs():
+        return (torch.empty((batch, gamma, s.hidden), dtype=torch.float32, device="cuda"),
+                torch.empty((batch, gamma), dtype=torch.int32, device="cuda"),
+                torch.empty((batch, gamma + 1), dtype=torch.int32, device="cuda"),
+                torch.empty((batch, gamma), dtype=torch.float32, device="cuda"))
+
+    a, b = outs(), outs()
+    D.select_and_head(dd, reps, acc, bon, *a, ws)
+    torch.cuda.synchronize()
+    assert ws.status() == 0 and ws.head_fallback() == 0
+    cand = D.branch_candidates_buffer(dd, batch)
+    D.branch_candidates(dd, reps, cand, ws)
+    D.select_and_head_cand(dd, reps, cand, acc, bon, *b, ws)
+    torch.cuda.synchronize()
+    assert ws.status() == 0 and ws.head_fallback() == 0
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
