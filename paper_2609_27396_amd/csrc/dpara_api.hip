@@ -565,6 +565,52 @@ int dpara_ctx_append(const dpara_config_t* cfg, const dpara_weights_t* w, const 
   int* status = at<int>(ws, 0);
   const size_t layer_elems = (size_t)ctx->batch_cap * nkv * ctx->ctx_cap * hd;
   const size_t esz = p.esz;
+  // More than 320 feature rows of a bf16 drafter with 128-wide heads: the projection reads the
+  // features where they are and its epilogue writes the caches, over all rows of up to
+  // kMaxKvRows at a time; the RoPE table of those rows takes the fp32 planes' region.  Fewer rows
+  // fill the chip only with K split over workgroups, whose planes kv_store adds up.
+  const int64_t rows = (int64_t)batch * n_max;
+  if (dt == DPARA_BF16 && hd == 128 && rows > 320 && rows <= INT32_MAX / 2 && H % 128 == 0 && H >= 256 &&
+      nkv % 2 == 0) {
+    const int64_t fit = (int64_t)(p.rope_app - p.KV32) / (64 * 8);
+    const int most = fit < kMaxKvRows ? (int)fit : kMaxKvRows;
+    const int chunks = (int)((rows + most - 1) / most), CR = (int)((rows + chunks - 1) / chunks);
+    for (int r0 = 0; r0 < rows; r0 += CR) {
+      const int n = rows - r0 < CR ? (int)(rows - r0) : CR;
+      HIP_TRY(launch_rope_rows(n, r0, n_max, hd, cfg->rope_base, ctx->ctx_len, at<float2>(ws, p.KV32), st), "rope_rows");
+      for (int l0 = 0; l0 < cfg->n_layers; l0 += kMaxAppendLayers) {
+        const int nl = cfg->n_layers - l0 < kMaxAppendLayers ? cfg->n_layers - l0 : kMaxAppendLayers;
+        GemmArgs g{};
+        g.A = (const char*)feats + (size_t)r0 * H * esz;
+        g.lda = H;
+        g.seg_rows = nkv * hd;
+        for (int j = 0; j < nl; ++j) {
+          g.seg[2 * j] = w->layers[l0 + j].wk;
+          g.seg[2 * j + 1] = w->layers[l0 + j].wv;
+          g.kv.kn[j] = w->layers[l0 + j].k_norm;
+        }
+        g.M = n;
+        g.N = nl * 2 * nkv * hd;
+        g.K = H;
+        g.kv.r0 = r0;
+        g.kv.n_max = n_max;
+        g.kv.n_kv = nkv;
+        g.kv.cap = ctx->ctx_cap;
+        g.kv.qk_norm = cfg->qk_norm;
+        g.kv.eps = cfg->rms_eps;
+        g.kv.table = at<float2>(ws, p.KV32);
+        g.kv.n_new = n_new;
+        g.kv.ctx_len = ctx->ctx_len;
+        g.kv.Kc = (char*)ctx->k + l0 * layer_elems * esz;
+        g.kv.Vc = (char*)ctx->v + l0 * layer_elems * esz;
+        g.kv.layer_elems = layer_elems;
+        Phase ph("append_gemm", st);
+        HIP_TRY(launch_gemm(A_BF16, EPI_KV, g, st), "append kv gemm");
+      }
+    }
+    HIP_TRY(launch_ctx_len_update(batch, n_max, ctx->ctx_cap, n_new, ctx->ctx_len, status, st), "ctx_len_update");
+    return DPARA_OK;
+  }
   const int CH = n_max < p.CH ? n_max : p.CH;  // rows per request per chunk
   for (int c0 = 0; c0 < n_max; c0 += CH) {
     HIP_TRY(launch_gather_feats(dt, batch, CH, c0, n_max, H, feats, at<void>(ws, p.F), st), "gather_feats");

@@ -129,6 +129,15 @@ __global__ void rope_table_kernel(int n_pos, int hd, double base, const int* ctx
   rope_entry(blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x, n_pos, hd, base, ctx_len, pos_off, table);
 }
 
+__global__ void rope_rows_kernel(int n, int r0, int n_max, int hd, double base, const int* ctx_len, float2* table) {
+  const int half = hd / 2, idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= n * half) return;
+  const int r = r0 + idx / half, b = r / n_max;
+  float c, s;
+  rope_cs(max(ctx_len[b], 0) + r - b * n_max, idx % half, hd, base, &c, &s);
+  table[idx] = make_float2(c, s);
+}
+
 // The backbone's first two steps in one launch: blocks x < R assemble rows, the blocks past R
 // fill the RoPE table (256 entries each).
 template <typename T>
@@ -446,6 +455,13 @@ hipError_t launch_qk_norm_rope(int dtype, int B, int R, int Rp, int gamma, int n
   if (dtype == 1)
     return hd == 128 ? go(qk_norm_rope<bf16_t, 128>, (bf16_t*)nullptr) : go(qk_norm_rope<bf16_t, 64>, (bf16_t*)nullptr);
   return hd == 128 ? go(qk_norm_rope<float, 128>, (float*)nullptr) : go(qk_norm_rope<float, 64>, (float*)nullptr);
+}
+
+hipError_t launch_rope_rows(int n, int r0, int n_max, int hd, float base, const int* ctx_len, float2* table,
+                            hipStream_t st) {
+  hipLaunchKernelGGL(rope_rows_kernel, dim3((n * (hd / 2) + 255) / 256), dim3(256), 0, st, n, r0, n_max, hd, (double)base,
+                     ctx_len, table);
+  return hipGetLastError();
 }
 
 hipError_t launch_gather_feats(int dtype, int B, int CH, int c0, int n_max, int H, const void* feats,

@@ -655,7 +655,7 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st) {
     if (amode != A_BF16 || a.ldc < (a.N + 127) / 128) return hipErrorInvalidValue;
     return run_pipe<192, 128, 2, 2, 2, 128, EPI_TOP2, 0>(a, st);
   }
-  if (epi == EPI_QKV) return hipErrorInvalidValue;  // the large-M kernel's epilogue
+  if (epi == EPI_QKV || epi == EPI_KV) return hipErrorInvalidValue;  // the large-M kernel's epilogues
   if (amode == A_BF16_FRAG) {
     return epi == EPI_STORE_F32 ? run_adir(a, st) : hipErrorInvalidValue;
   }

@@ -57,7 +57,7 @@ constexpr int kGroupM = 8;
 // 433 -> 391).  The QKV epilogue's V^T staging (2 KB a wave) leaves no room for the third slot
 // at 256 rows.  A tail tile's K step is short (36 KB of loads), so there both operands run two or
 // three steps ahead.
-__host__ __device__ constexpr int ring_depth(int epi, int bm) { return epi == EPI_QKV && bm == 256 ? 2 : 3; }
+__host__ __device__ constexpr int ring_depth(int epi, int bm) { return (epi == EPI_QKV || epi == EPI_KV) && bm == 256 ? 2 : 3; }
 __host__ __device__ constexpr int tail_depth(int epi, int tail) { return epi == EPI_QKV || tail == 128 ? 3 : 4; }
 constexpr int kStageWave = 2048;
 
@@ -112,6 +112,65 @@ struct HalfPlan {
   static constexpr int read_a(int m) { return m < LO ? (last_a() + 1 < NG ? last_a() + 1 : NG - 1) : (DB + m - LO) / RATE; }
 };
 
+// Parts of the epilogues that hold one 128-wide head a wave column: x[ni] are a row's columns
+// ni * 16 + lc * 4 .., the rest of its 128 sits in the three lanes 16 apart.
+// x * (1 / sqrt(ss / 128 + eps)) * g; gain: the lane's first.
+__device__ __forceinline__ void head_norm(f32x4_t (&x)[8], const float* gain, float eps) {
+  float ss = 0.f;
+#pragma unroll
+  for (int ni = 0; ni < 8; ++ni)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) ss += x[ni][r] * x[ni][r];
+  ss = lanes4_sum(ss);
+  const float rn = 1.0f / sqrtf(ss / 128.0f + eps);
+#pragma unroll
+  for (int ni = 0; ni < 8; ++ni) {
+    const float4 g = *(const float4*)(gain + ni * 16);
+    x[ni][0] = x[ni][0] * rn * g.x;
+    x[ni][1] = x[ni][1] * rn * g.y;
+    x[ni][2] = x[ni][2] * rn * g.z;
+    x[ni][3] = x[ni][3] * rn * g.w;
+  }
+}
+
+// x_d cos - x_{d+64} sin and x_{d+64} cos + x_d sin (both operands in the lane) as bf16; cs, dst: the
+// lane's first (cos, sin) and destination.
+__device__ __forceinline__ void head_rope(const f32x4_t (&x)[8], const float2* cs, bf16_t* dst) {
+#pragma unroll
+  for (int ni = 0; ni < 4; ++ni) {
+    const float4 c01 = *(const float4*)(cs + ni * 16), c23 = *(const float4*)(cs + ni * 16 + 2);
+    const float co[4] = {c01.x, c01.z, c23.x, c23.z}, si[4] = {c01.y, c01.w, c23.y, c23.w};
+    float lo[4], hi[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float l = x[ni][r], h = x[ni + 4][r];
+      lo[r] = l * co[r] + -1.f * h * si[r];
+      hi[r] = h * co[r] + 1.f * l * si[r];
+    }
+    *(uint2*)(dst + ni * 16) = pack4(lo[0], lo[1], lo[2], lo[3]);
+    *(uint2*)(dst + ni * 16 + 64) = pack4(hi[0], hi[1], hi[2], hi[3]);
+  }
+}
+
+// The wave's WM rows as columns of a [128][stride] matrix: 16 head dimensions at a time through its
+// LDS, so that a store covers consecutive rows.  Lane l stores row l at dst where `on`.
+template <int WM>
+__device__ __forceinline__ void head_transposed(const f32x4_t (&acc)[WM / 16][8], bf16_t* stg, int lane, bool on,
+                                                bf16_t* dst, int stride) {
+  const int lr = lane & 15, lc = lane >> 4;
+#pragma unroll
+  for (int ni = 0; ni < 8; ++ni) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int mi = 0; mi < WM / 16; ++mi)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) stg[(lc * 4 + r) * 64 + mi * 16 + lr] = f2bf(acc[mi][ni][r]);
+    if (on)
+#pragma unroll 8
+      for (int d = 0; d < 16; ++d) dst[(int64_t)(ni * 16 + d) * stride] = stg[d * 64 + lane];
+  }
+}
+
 // Epilogue of one BM x BN tile whose wave (wm, wn) holds rows m0 + wm * WM .. and columns
 // wn * WN .. of column tile nt: lane (lr, lc) has row .. + mi * 16 + lr and the four columns
 // ni * 16 + lc * 4 .. of every fragment (mi, ni); rows from m_end on are not the tile's.  stg: kStageWave bytes of LDS of this wave alone.
@@ -121,11 +180,46 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
   constexpr int FM = WM / 16, FN = WN / 16;
   const int lr = lane & 15, lc = lane >> 4;
   const int row_w = row0 + lr;
+  if constexpr (EPI == EPI_KV) {
+    static_assert(WN == 128, "one 128-wide head per wave column");
+    // as EPI_QKV below, at each row's position in the caches
+    const KvEpi& e = a.kv;
+    const int head = nt * WNW + wn, l = head / (2 * e.n_kv), slot = head - l * 2 * e.n_kv;
+    if (head * 128 >= a.N) return;
+    // this lane's row: its request, position, and whether it is stored
+    auto place = [&](int row, int& b, int& pos) {
+      const int r = e.r0 + min(row, m_end - 1);
+      b = r / e.n_max;
+      const int c = r - b * e.n_max;
+      pos = max(e.ctx_len[b], 0) + c;
+      return row < m_end && c < min(e.n_new[b], e.n_max) && pos < e.cap;
+    };
+    if (slot < e.n_kv) {
+      const float* gain = e.kn[0];
+#pragma unroll
+      for (int j = 1; j < 8; ++j) gain = l == j ? e.kn[j] : gain;  // (an indexed argument goes to scratch)
+      gain += lc * 4;
+#pragma unroll
+      for (int mi = 0; mi < FM; ++mi) {
+        __builtin_amdgcn_sched_barrier(0);
+        const int row = row_w + mi * 16;
+        int b, pos;
+        const bool on = place(row, b, pos);
+        if (e.qk_norm) head_norm(acc[mi], gain, e.eps);
+        if (on)
+          head_rope(acc[mi], e.table + (int64_t)row * 64 + lc * 4,
+                    (bf16_t*)e.Kc + l * e.layer_elems + ((int64_t)(b * e.n_kv + slot) * e.cap + pos) * 128 + lc * 4);
+      }
+    } else {
+      int b, pos;
+      const bool on = place(row0 + lane, b, pos) && lane < WM;
+      bf16_t* dst = (bf16_t*)e.Vc + l * e.layer_elems + (int64_t)(b * e.n_kv + slot - e.n_kv) * 128 * e.cap + pos;
+      head_transposed<WM>(acc, stg, lane, on, dst, e.cap);
+    }
+    return;
+  }
   if constexpr (EPI == EPI_QKV) {
     static_assert(WN == 128, "one 128-wide head per wave column");
-    // y = x * (1 / sqrt(ss / 128 + eps)) * g over the head's 128 columns (32 in this lane, the
-    // rest in the three lanes 16 apart), then y_d = y_d cos - y_{d+64} sin and
-    // y_{d+64} = y_{d+64} cos + y_d sin, whose operands sit in the same lane.
     const QkvEpi& e = a.qkv;
     const int slot = nt * WNW + wn, grp = e.n_q / e.n_kv;
     if (slot >= e.n_q + 2 * e.n_kv) return;
@@ -136,60 +230,17 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
       for (int mi = 0; mi < FM; ++mi) {
         __builtin_amdgcn_sched_barrier(0);
         const int row = row_w + mi * 16, rc = min(row, m_end - 1), b = rc / e.R, rr = rc - b * e.R;
-        if (e.qk_norm) {
-          float ss = 0.f;
-#pragma unroll
-          for (int ni = 0; ni < FN; ++ni)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) ss += acc[mi][ni][r] * acc[mi][ni][r];
-          ss = lanes4_sum(ss);
-          const float rn = 1.0f / sqrtf(ss / 128.0f + e.eps);
-#pragma unroll
-          for (int ni = 0; ni < FN; ++ni) {
-            const float4 g = *(const float4*)(gain + ni * 16);
-            acc[mi][ni][0] = acc[mi][ni][0] * rn * g.x;
-            acc[mi][ni][1] = acc[mi][ni][1] * rn * g.y;
-            acc[mi][ni][2] = acc[mi][ni][2] * rn * g.z;
-            acc[mi][ni][3] = acc[mi][ni][3] * rn * g.w;
-          }
-        }
+        if (e.qk_norm) head_norm(acc[mi], gain, e.eps);
         const float2* cs = e.table + ((int64_t)b * (2 * e.gamma + 1) + row_pos_offset(rr, e.gamma)) * 64 + lc * 4;
         bf16_t* dst = isq ? (bf16_t*)e.Q + (((int64_t)(b * e.n_kv + slot / grp) * grp + slot % grp) * e.R + rr) * 128
                           : (bf16_t*)e.Kb + ((int64_t)(b * e.n_kv + (slot - e.n_q)) * e.Rp + rr) * 128;
-        dst += lc * 4;
-#pragma unroll
-        for (int ni = 0; ni < FN / 2; ++ni) {
-          const float4 c01 = *(const float4*)(cs + ni * 16), c23 = *(const float4*)(cs + ni * 16 + 2);
-          const float co[4] = {c01.x, c01.z, c23.x, c23.z}, si[4] = {c01.y, c01.w, c23.y, c23.w};
-          float lo[4], hi[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float l = acc[mi][ni][r], h = acc[mi][ni + FN / 2][r];
-            lo[r] = l * co[r] + -1.f * h * si[r];
-            hi[r] = h * co[r] + 1.f * l * si[r];
-          }
-          if (row < m_end) {
-            *(uint2*)(dst + ni * 16) = pack4(lo[0], lo[1], lo[2], lo[3]);
-            *(uint2*)(dst + ni * 16 + 64) = pack4(hi[0], hi[1], hi[2], hi[3]);
-          }
-        }
+        if (row < m_end) head_rope(acc[mi], cs, dst + lc * 4);
       }
     } else {
-      // V^T [128][Rp] per request: 16 columns at a time through this wave's LDS, so that a store
-      // covers the wave's consecutive rows of one head dimension
+      // V^T [128][Rp] per request
       const int row = row0 + lane, rc = min(row, m_end - 1), b = rc / e.R;
       bf16_t* dst = (bf16_t*)e.Vb + (int64_t)(b * e.n_kv + (slot - e.n_q - e.n_kv)) * 128 * e.Rp + (rc - b * e.R);
-#pragma unroll
-      for (int ni = 0; ni < FN; ++ni) {
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int mi = 0; mi < FM; ++mi)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) stg[(lc * 4 + r) * 64 + mi * 16 + lr] = f2bf(acc[mi][ni][r]);
-        if (lane < WM && row < m_end)
-#pragma unroll 8
-          for (int d = 0; d < 16; ++d) dst[(int64_t)(ni * 16 + d) * e.Rp] = stg[d * 64 + lane];
-      }
+      head_transposed<WM>(acc, stg, lane, lane < WM && row < m_end, dst, e.Rp);
     }
     return;
   }
@@ -527,6 +578,42 @@ gemm_mid_kernel(GemmArgs a, int MT, int NT, int rows) {
                                                      smem);
 }
 
+// The context append over more than 320 feature rows (EPI_KV): all layers' K|V projections straight
+// into the caches.  Row tiles whose rows are all past their request's count or the cache's end are
+// left out: every workgroup finds the tiles that are not (at most 64, one a lane).  Bound by the
+// MFMAs and the DMA, as above.  Three prompts of 1250, 955 and 478 rows, five Qwen3-8B layers: 246 us;
+// fp32 planes in chunks of 867 rows, a copy of the features and a store pass took 490.
+template <int BM>
+__global__ __launch_bounds__(512, 2) void gemm_kv_kernel(GemmArgs a, int MT, int NT) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int NB = ring_depth(EPI_KV, BM), NA = BM == 256 ? 2 : 3;
+  debug_poison_lds<(NA * BM + NB * 256) * 128>(smem);
+  const KvEpi& e = a.kv;
+  const int t = threadIdx.x & 63;
+  bool live = false;
+  if (t < MT) {
+    const int r = e.r0 + t * BM, end = e.r0 + min((t + 1) * BM, a.M);
+    int b = r / e.n_max, c = r - b * e.n_max;
+    for (int left = end - r; left > 0 && !live; ++b) {
+      live = c < min(e.n_new[b], e.n_max) && max(e.ctx_len[b], 0) + c < e.cap;
+      left -= e.n_max - c;
+      c = 0;
+    }
+  }
+  const unsigned long long mask = __ballot(live);
+  const int n_live = __popcll(mask), w = blockIdx.x, grid = gridDim.x, total = n_live * NT;
+  if (w >= total) return;
+  large_tiles<BM, 256, 4, 2, NA, NB, EPI_KV, 0>(a, (total - w + grid - 1) / grid, BM,
+                                                [&](int i, int& s, int& m0, int& nt) {
+                                                  int mt;
+                                                  large_tile(w + grid * i, total, n_live, NT, s, mt, nt);
+                                                  unsigned long long m = mask;
+                                                  for (; mt > 0; --mt) m &= m - 1;
+                                                  m0 = (__ffsll(m) - 1) * BM;
+                                                },
+                                                smem);
+}
+
 constexpr int kCus = 256;
 
 // Rows of the tail tiles (0: the last row tile runs as a full one) and their cost against a full
@@ -618,6 +705,29 @@ hipError_t pick_large(const GemmArgs& a, hipStream_t st) {
     if (t.BN == 192) return run_large<256, 192, EPI>(a, st);
   if (t.BM == 192) return run_large<192, 256, EPI>(a, st);
   return run_large<256, 256, EPI>(a, st);
+}
+
+template <int BM>
+hipError_t run_kv(const GemmArgs& a, hipStream_t st) {
+  constexpr int NB = ring_depth(EPI_KV, BM), NA = BM == 256 ? 2 : 3;
+  constexpr int lds = (NA * BM + NB * 256) * 128 + 8 * kStageWave;
+  static_assert(lds <= 163840, "LDS");
+  auto kern = gemm_kv_kernel<BM>;
+  static const hipError_t attr =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (attr != hipSuccess) return attr;
+  const int MT = (a.M + BM - 1) / BM, NT = (a.N + 255) / 256;
+  hipLaunchKernelGGL(kern, dim3(MT * NT < kCus ? MT * NT : kCus), dim3(512), lds, st, a, MT, NT);
+  return hipGetLastError();
+}
+
+// 256-row tiles, or 128 where the rounds over the CUs cost less (a K step of 128 x 256 takes about
+// 0.6 of one of 256 x 256).
+hipError_t pick_kv(const GemmArgs& a, hipStream_t st) {
+  const int NT = (a.N + 255) / 256;
+  const int r256 = ((a.M + 255) / 256 * NT + kCus - 1) / kCus, r128 = ((a.M + 127) / 128 * NT + kCus - 1) / kCus;
+  if (a.M <= 64 * 128 && r128 * 0.6 < r256) return run_kv<128>(a, st);
+  return run_kv<256>(a, st);
 }
 
 template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, int STREAM>
@@ -719,6 +829,7 @@ bool gemm_large_supported(int epi, const GemmArgs& a) {
     case EPI_STORE_BF16:
     case EPI_TOP2:
     case EPI_QKV: return true;
+    case EPI_KV: return a.M <= kMaxKvRows && a.seg_rows == a.kv.n_kv * 128 && a.kv.n_max > 0;
     default: return false;
   }
 }
@@ -745,6 +856,7 @@ hipError_t launch_gemm_large(int epi, const GemmArgs& a, hipStream_t st) {
     case EPI_STORE_F32: return pick_large<EPI_STORE_F32>(a, st);
     case EPI_STORE_BF16: return run_large<256, 256, EPI_STORE_BF16>(a, st);
     case EPI_TOP2: return run_large<256, 256, EPI_TOP2>(a, st);
+    case EPI_KV: return pick_kv(a, st);
     default: return pick_large<EPI_QKV>(a, st);
   }
 }

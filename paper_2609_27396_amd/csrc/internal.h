@@ -22,7 +22,7 @@ struct Phase {
 // C[M, N] (op)= A[M, K] . B[N, K]^T with B given in up to three row segments
 // (rows [0, n1) from B0, [n1, n2) from B1, [n2, N) from B2), or, with seg_rows > 0 (not for
 // EPI_SWIGLU), in equal segments: row n from seg[n / seg_rows], row n % seg_rows.
-enum GemmEpi { EPI_STORE_F32 = 0, EPI_ADD_F32 = 1, EPI_SWIGLU = 2, EPI_STORE_BF16 = 3, EPI_TOP2 = 4, EPI_QKV = 5 };
+enum GemmEpi { EPI_STORE_F32 = 0, EPI_ADD_F32 = 1, EPI_SWIGLU = 2, EPI_STORE_BF16 = 3, EPI_TOP2 = 4, EPI_QKV = 5, EPI_KV = 6 };
 
 // Parameters of the EPI_QKV epilogue: the Q|K|V projection of R rows per request written as
 // the attention kernel's bf16 operands (Q [B, n_kv, grp * R, 128], in-block K [B, n_kv, Rp, 128],
@@ -37,6 +37,22 @@ struct QkvEpi {
   void* Q = nullptr;
   void* Kb = nullptr;
   void* Vb = nullptr;
+};
+// Parameters of the EPI_KV epilogue: the K|V projections of a context append (up to eight layers,
+// seg[2 j] = W_k and seg[2 j + 1] = W_v of layer j, head_dim 128) written into the caches.  Row r
+// of the product is row r0 + r of the [batch, n_max] feature rows: entry c of request b, at position
+// ctx_len[b] + c; entries from n_new[b] on and positions from cap on are not stored.  K rows get
+// the k-norm (qk_norm != 0, gains kn[j]) and RoPE (table: (cos, sin) of row r, 64 frequencies).
+struct KvEpi {
+  int r0 = 0, n_max = 1, n_kv = 0, cap = 0, qk_norm = 0;
+  float eps = 0.f;
+  const float* kn[8] = {};
+  const float2* table = nullptr;
+  const int* n_new = nullptr;
+  const int* ctx_len = nullptr;
+  void* Kc = nullptr;  // layer 0's caches; the other layers' follow layer_elems entries apart
+  void* Vc = nullptr;
+  int64_t layer_elems = 0;
 };
 // A_BF16: A is bf16, row-major with leading dimension lda.  A_F32: float32 FMA kernel
 // (the float32 model path; B is then float32 too).
@@ -77,6 +93,7 @@ struct GemmArgs {
   int seg_rows = 0;               // > 0: B rows from seg[] (N <= kMaxGemmSegs * seg_rows)
   const void* seg[16] = {};
   QkvEpi qkv{};  // EPI_QKV only (bf16, head_dim 128, gemm_large_supported(), no split-K)
+  KvEpi kv{};    // EPI_KV only (the same)
 };
 
 constexpr int kMaxGemmSegs = 16;
@@ -91,6 +108,7 @@ int gemm_mid_splits(int N, int K);
 bool gemm_large_supported(int epi, const GemmArgs& a);
 hipError_t launch_gemm_large(int epi, const GemmArgs& a, hipStream_t st);
 int gemm_large_splits(int M, int N, int K);  // split-K planes of its float32 store
+constexpr int kMaxKvRows = 64 * 256;         // rows of one EPI_KV launch
 // Split-K factor launch_gemm uses for a bf16 fp32-store GEMM of this shape (1 = no split).
 // The consumer of C sums the S planes in order 0..S-1.  seg: greatest common divisor of the
 // boundaries of the weight's row segments (0: one segment).
@@ -142,6 +160,10 @@ hipError_t launch_qk_norm_rope(int dtype, int B, int R, int Rp, int gamma, int n
                                int qk_norm, float eps, const float* QKV, int S, const float* qn,
                                const float* kn, const float2* table, void* Q, void* Kb,
                                void* Vb, hipStream_t st);
+// RoPE table of rows r0 .. r0 + n - 1 of [batch, n_max] appended rows: row r0 + i is entry c of request
+// b, at position ctx_len[b] + c.
+hipError_t launch_rope_rows(int n, int r0, int n_max, int hd, float base, const int* ctx_len, float2* table,
+                            hipStream_t st);
 hipError_t launch_gather_feats(int dtype, int B, int CH, int c0, int n_max, int H,
                                const void* feats, void* F, hipStream_t st);
 // K/V of the appended rows for nl consecutive layers: KV holds S fp32 planes

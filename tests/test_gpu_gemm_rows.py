@@ -107,3 +107,48 @@ def test_candidate_rows_around_tile_edges(batch, gamma):
     assert ws.status() == 0 and ws.head_fallback() == 0
     for x, y in zip(a, b):
         assert torch.equal(x, y)
+
+
+# rows of one append: just above 320, row tiles of padding only, two layer groups, an append past the
+# cache's end, and more rows than one launch takes
+@pytest.mark.parametrize("layers,starts,counts,n_max,cap,step", [
+    (2, [0, 3, 0], [107, 1, 106], 107, 128, 53),
+    (9, [5, 0, 70, 9], [700, 0, 133, -2], 700, 640, 70),
+    (1, [1, 64], [9000, 4097], 9000, 9088, 160),
+])
+def test_prompt_append_is_its_short_appends(layers, starts, counts, n_max, cap, step):
+    """A prompt's rows appended at once (one projection that writes the caches) against the same
+    rows in appends of at most 320 rows (projection, then a store pass): lengths equal, entries
+    nobody appended untouched, the others within one bf16 rounding (float32 sums in another order)."""
+    from paper_2609_27396_amd import dpara as D
+    B = len(starts)
+    assert B * n_max > 320 and B * step <= 320
+    s = synth.DrafterShape(n_layers=layers, hidden=384, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn=256, vocab=500,
+                           gamma=4, ar_rank=64, qk_norm=True, dtype="bf16")
+    _say("case prompt append", layers, B, n_max)
+    dd = D.DeviceDrafter(s, synth.make_weights(s, seed=31, gain_jitter=0.1))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(layers)
+    feats = torch.empty((B, n_max, s.hidden), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+
+    def run(step):
+        ctx = D.DeviceContext(s, B, cap)
+        ctx.k.fill_(7.0)
+        ctx.v.fill_(-7.0)
+        ctx.ctx_len.copy_(torch.tensor(starts, dtype=torch.int32))
+        ws = D.Workspace(dd.cfg, B, cap)
+        for c0 in range(0, n_max, step):
+            n = min(step, n_max - c0)
+            new = torch.tensor([c if c < 0 else min(max(c - c0, 0), n) for c in counts], dtype=torch.int32, device="cuda")
+            D.ctx_append(dd, ctx, feats[:, c0:c0 + n].contiguous(), new, ws)
+        torch.cuda.synchronize()
+        return ctx, ws.status()
+
+    one, status = run(n_max)
+    ref, ref_status = run(step)
+    assert status == ref_status
+    assert torch.equal(one.ctx_len, ref.ctx_len)
+    for a, b, mark in ((one.k, ref.k, 7.0), (one.v, ref.v, -7.0)):
+        assert torch.equal(a == mark, b == mark)
+        a, b = a.float(), b.float()
+        assert bool(((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5).all())
