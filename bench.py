@@ -35,7 +35,7 @@ PEAK_HBM_GBS = 8000.0
 PEAK_BF16_TFLOPS = 2500.0
 PEAK_F32_TFLOPS = 157.3
 COPY_PROBE_BYTES = 256 << 20
-GATEUP_KERNEL_SMALL_M = "gemm_mid_kernel<160, 192, 2, 2, 3, 3, 2, 0>"  # gate/up SwiGLU at 257-320 rows
+GATEUP_KERNEL_SMALL_M = "gemm_mid_kernel<160, 192, 2, 2, 3, 3, 2, 0, 1>"  # gate/up SwiGLU at 257-320 rows
 
 
 def log(*a):

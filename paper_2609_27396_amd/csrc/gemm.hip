@@ -637,10 +637,9 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st) {
     // 32 rows (two requests): the same 128-deep stages in a 3-deep ring, 15% faster than the
     // 64-row tile with half its rows idle (batch-2 head 325-345 -> 282 us on MI355X).
     if (a.M <= 32) return run_pipe<32, 128, 1, 4, 3, 256, EPI_STORE_F32, 1>(a, st);
+    if (epi == EPI_STORE_F32 && gemm_dual_supported(a)) return launch_gemm_dual(a, st);
+    // more rows with a K that is no multiple of 128 or weights in segments
     if (a.M <= 64) return run_pipe<64, 128, 2, 2, 3, 128, EPI_STORE_F32, 1>(a, st);
-    // 129-256 rows (batch 9-16): one 256-row tile (both planes, 2-deep ring of 160 KB), so each
-    // weight tile is read once: the batch-16 head 860 -> 797 us.
-    if (a.M > 128 && a.M <= 256) return run_pipe<256, 128, 4, 2, 2, 128, EPI_STORE_F32, 1>(a, st);
     return run_pipe<128, 128, 4, 2, 3, 128, EPI_STORE_F32, 1>(a, st);
   }
   if (amode == A_BF16 && epi == EPI_TOP2 && a.ldc < (a.N + 127) / 128) return hipErrorInvalidValue;

@@ -322,17 +322,19 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
 // A list of n tiles of `rows` <= BM rows (item(i): K split s, first row m0, column tile nt) for
 // WMW x WNW waves; K a multiple of 128, at least 256 per split.  NA, NB: ring slots of A and B;
 // STREAM: the weights are read once, as non-temporal lines (the activations stay in L2).
-template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, int STREAM, typename Item>
+// PL: planes of A; two are a float32 operand's bf16 hi and lo parts (lo_off apart), whose rows share a
+// ring slot and which both meet every weight fragment, hi first.
+template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, int STREAM, int PL, typename Item>
 __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, int rows, const Item& item, unsigned char* smem) {
   constexpr int NW = WMW * WNW, WM = BM / WMW, WN = BN / WNW, FM = WM / 16, FN = WN / 16;
   constexpr int GR = 8 * NW;  // tile rows one DMA instruction of every wave loads
-  constexpr int AI = BM / GR, BI = BN / GR, ND = AI + BI;  // 1 KB DMA instructions per wave and K step
-  constexpr int A_SLOT = BM * 128, B_SLOT = BN * 128, B0 = NA * A_SLOT, RING = NA * A_SLOT + NB * B_SLOT;
+  constexpr int AG = BM / GR, AI = PL * AG, BI = BN / GR, ND = AI + BI;  // 1 KB DMA instructions per wave and K step
+  constexpr int A_SLOT = PL * BM * 128, B_SLOT = BN * 128, B0 = NA * A_SLOT, RING = NA * A_SLOT + NB * B_SLOT;
   // loads a step's barrier may leave in flight: those issued after the next step's (vmcnt counts
   // in order)
   static_assert(NA == NB || (NA == 2 && NB == 3), "ring depths");
   constexpr int LATER = NA == NB ? (NB - 2) * ND : BI;
-  using P = HalfPlan<FM, FN>;
+  using P = HalfPlan<PL * FM, FN>;
   static_assert(BM % GR == 0 && BN % GR == 0, "whole DMA groups");
   static_assert(EPI != EPI_SWIGLU || FN % 2 == 0, "gate and up fragments in pairs");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -350,9 +352,9 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, int rows, 
   constexpr int BP = EPI == EPI_SWIGLU ? 2 : 1;  // B parts: gate and up rows
   constexpr int BG = BI / BP;  // groups of a part
   static_assert(BG * BP == BI, "whole groups of a part");
-  int voff[AI > BG ? AI : BG];
+  int voff[AG > BG ? AG : BG];
 #pragma unroll
-  for (int q = 0; q < (AI > BG ? AI : BG); ++q)
+  for (int q = 0; q < (AG > BG ? AG : BG); ++q)
     voff[q] = (q * GR + wave * 8 + lrow) * K2 + (((lane & 7) ^ lrow) * 16);
   const char *pa, *pb[BP];  // the tile the next A load and the next B load belong to
   unsigned na, nb;          // valid bytes from there
@@ -389,8 +391,9 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, int rows, 
 #if defined(__HIP_DEVICE_COMPILE__)
     unsigned char* dst = smem + (q < AI ? as * A_SLOT : B0 + bs * B_SLOT) + (wave + NW * (q < AI ? q : q - AI)) * 1024;
     if (q < AI) {
-      const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)pa, 0, (int)na, 0x00020000);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)dst, 16, voff[q], ka * 128, 0, 0);
+      const char* p = PL > 1 && q >= AG ? pa + a.lo_off * 2 : pa;
+      const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)na, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)dst, 16, voff[q % AG], ka * 128, 0, 0);
     } else {
       const int j = q - AI;
       const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)pb[j / BG], 0, (int)nb, 0x00020000);
@@ -417,7 +420,7 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, int rows, 
     bf[P::bslot(h, n)] = *(const bf16x8_t*)(rb[h] + bs * B_SLOT + row * 128);
   };
   auto read_a = [&](int m, int as, int h) {
-    af[P::aslot(h, m)] = *(const bf16x8_t*)(ra[h] + as * A_SLOT + m * 2048);
+    af[P::aslot(h, m)] = *(const bf16x8_t*)(ra[h] + as * A_SLOT + (m / FM) * BM * 128 + (m % FM) * 2048);
   };
   constexpr int DPG = (ND + P::NG - 1) / P::NG;
   // One half of a K step: the MFMAs of register set h, the fragment reads of the next half
@@ -429,7 +432,7 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, int rows, 
       for (int n = 0; n < FN; ++n)
         if (P::read_b(n) == g) read_b(n, bs, h ^ 1);
 #pragma unroll
-      for (int m = 0; m < FM; ++m)
+      for (int m = 0; m < PL * FM; ++m)
         if (P::read_a(m) == g) read_a(m, as, h ^ 1);
       if (h == 1) {
 #pragma unroll
@@ -439,8 +442,8 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, int rows, 
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int t = g * P::GRP; t < (g + 1) * P::GRP; ++t) {
-        const int mi = P::mi(t), ni = P::ni(t);
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[P::bslot(h, ni)], af[P::aslot(h, mi)], acc[mi][ni], 0, 0, 0);
+        const int m = P::mi(t), mi = m % FM, ni = P::ni(t);
+        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[P::bslot(h, ni)], af[P::aslot(h, m)], acc[mi][ni], 0, 0, 0);
       }
       __builtin_amdgcn_s_setprio(0);
       __builtin_amdgcn_sched_barrier(0);
@@ -475,7 +478,7 @@ __device__ __forceinline__ void large_tiles(const GemmArgs& a, int n, int rows, 
 #pragma unroll
     for (int j = 0; j < FN; ++j) read_b(j, bs, 0);
 #pragma unroll
-    for (int i = 0; i < FM; ++i) read_a(i, as, 0);
+    for (int i = 0; i < PL * FM; ++i) read_a(i, as, 0);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -535,7 +538,7 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs a, LargePla
   // full tiles w, w + grid, ..; then this workgroup's share of the tails
   const int n_full = w < p.full ? (p.full - w + p.grid - 1) / p.grid : 0;
   if (n_full > 0)
-    large_tiles<BM, BN, 4, 2, 2, NB, EPI, 0>(a, n_full, BM, [&](int i, int& s, int& m0, int& nt) {
+    large_tiles<BM, BN, 4, 2, 2, NB, EPI, 0, 1>(a, n_full, BM, [&](int i, int& s, int& m0, int& nt) {
       int mt;
       large_tile(w + p.grid * i, p.full, p.mtf, p.NT, s, mt, nt);
       m0 = mt * BM;
@@ -550,7 +553,7 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs a, LargePla
     constexpr int TD = tail_depth(EPI, TAIL);
     // 64 rows: 2 x 4 waves where 64 columns a wave will do (a third fewer LDS reads)
     constexpr int WNW = TAIL == 64 && BN == 256 && EPI != EPI_QKV && EPI != EPI_TOP2 ? 4 : 2;
-    large_tiles<TAIL, BN, 8 / WNW, WNW, TD, TD, EPI, 0>(
+    large_tiles<TAIL, BN, 8 / WNW, WNW, TD, TD, EPI, 0, 1>(
         a, n1 + n2, TAIL, [&](int i, int& s, int& m0, int& nt) {
           const int t = i < n1 ? fr + p.nfree * i : p.tails1 + w + p.grid * (i - n1);
           s = t / p.NT;
@@ -562,14 +565,15 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs a, LargePla
 
 // 65 to 320 rows: weight streaming.  One or a few row tiles of equal height cover the rows, so the
 // weights are read once from HBM; workgroups walk the tiles as above, one or two to a CU.
-template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, int STREAM>
-__global__ __launch_bounds__(64 * WMW * WNW, (NA * BM + NB * BN) * 128 <= 81920 ? WMW * WNW / 2 : WMW * WNW / 4) void
+constexpr int mid_ring(int BM, int BN, int NA, int NB, int PL) { return (NA * PL * BM + NB * BN) * 128; }
+template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, int STREAM, int PL>
+__global__ __launch_bounds__(64 * WMW * WNW, mid_ring(BM, BN, NA, NB, PL) <= 81920 ? WMW * WNW / 2 : WMW * WNW / 4) void
 gemm_mid_kernel(GemmArgs a, int MT, int NT, int rows) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (a.only_if && *a.only_if == 0) return;
-  debug_poison_lds<(NA * BM + NB * BN) * 128>(smem);
+  debug_poison_lds<mid_ring(BM, BN, NA, NB, PL)>(smem);
   const int w = blockIdx.x, grid = gridDim.x, total = MT * NT * a.splits;
-  large_tiles<BM, BN, WMW, WNW, NA, NB, EPI, STREAM>(a, (total - w + grid - 1) / grid, rows,
+  large_tiles<BM, BN, WMW, WNW, NA, NB, EPI, STREAM, PL>(a, (total - w + grid - 1) / grid, rows,
                                                      [&](int i, int& s, int& m0, int& nt) {
                                                        int mt;
                                                        large_tile(w + grid * i, total, MT, NT, s, mt, nt);
@@ -603,7 +607,7 @@ __global__ __launch_bounds__(512, 2) void gemm_kv_kernel(GemmArgs a, int MT, int
   const unsigned long long mask = __ballot(live);
   const int n_live = __popcll(mask), w = blockIdx.x, grid = gridDim.x, total = n_live * NT;
   if (w >= total) return;
-  large_tiles<BM, 256, 4, 2, NA, NB, EPI_KV, 0>(a, (total - w + grid - 1) / grid, BM,
+  large_tiles<BM, 256, 4, 2, NA, NB, EPI_KV, 0, 1>(a, (total - w + grid - 1) / grid, BM,
                                                 [&](int i, int& s, int& m0, int& nt) {
                                                   int mt;
                                                   large_tile(w + grid * i, total, n_live, NT, s, mt, nt);
@@ -730,11 +734,11 @@ hipError_t pick_kv(const GemmArgs& a, hipStream_t st) {
   return run_kv<256>(a, st);
 }
 
-template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, int STREAM>
+template <int BM, int BN, int WMW, int WNW, int NA, int NB, int EPI, int STREAM, int PL = 1>
 hipError_t run_mid(const GemmArgs& a, hipStream_t st) {
-  constexpr int lds = (NA * BM + NB * BN) * 128;
+  constexpr int lds = mid_ring(BM, BN, NA, NB, PL);
   static_assert(lds <= 163840, "LDS");
-  auto kern = gemm_mid_kernel<BM, BN, WMW, WNW, NA, NB, EPI, STREAM>;
+  auto kern = gemm_mid_kernel<BM, BN, WMW, WNW, NA, NB, EPI, STREAM, PL>;
   static const hipError_t attr =
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (attr != hipSuccess) return attr;
@@ -814,6 +818,21 @@ hipError_t launch_gemm_mid(int epi, const GemmArgs& a, hipStream_t st) {
     case EPI_STORE_BF16: return pick_mid<EPI_STORE_BF16>(a, st);
     default: return pick_mid<EPI_TOP2>(a, st);
   }
+}
+
+bool gemm_dual_supported(const GemmArgs& a) {
+  return a.M > 32 && a.K % 128 == 0 && a.K >= 256 && a.lda == a.K && a.splits == 1 && a.seg_rows == 0 && a.n1 >= a.N;
+}
+
+hipError_t launch_gemm_dual(const GemmArgs& a, hipStream_t st) {
+  if (!gemm_dual_supported(a)) return hipErrorInvalidValue;
+  // 320 columns: Qwen3's vocabulary in two rounds of the CUs, each weight fragment read from LDS for
+  // both planes of all rows.  128 rows x 151936 x 4096: 290 us against 373 for 128 x 128 tiles with a
+  // wait for every fragment of a K step; from 129 rows on two or more row tiles share a weight tile
+  // from L2 (208 rows: the sampled head 1024 -> 949).
+  if (a.M <= 64) return run_mid<64, 320, 4, 2, 2, 3, EPI_STORE_F32, 1, 2>(a, st);
+  if (a.M <= 128) return run_mid<128, 320, 4, 2, 2, 2, EPI_STORE_F32, 1, 2>(a, st);
+  return run_mid<128, 320, 4, 2, 2, 2, EPI_STORE_F32, 0, 2>(a, st);
 }
 
 bool gemm_large_supported(int epi, const GemmArgs& a) {

@@ -103,6 +103,9 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st);
 bool gemm_mid_supported(int epi, const GemmArgs& a);
 hipError_t launch_gemm_mid(int epi, const GemmArgs& a, hipStream_t st);
 int gemm_mid_splits(int N, int K);
+// The same for an A of two planes (A_BF16_DUAL, float32 store) over more than 32 rows.
+bool gemm_dual_supported(const GemmArgs& a);
+hipError_t launch_gemm_dual(const GemmArgs& a, hipStream_t st);
 // The persistent kernel for more than 320 bf16 rows (gemm_large.hip): whether it takes this
 // call, and its launch.
 bool gemm_large_supported(int epi, const GemmArgs& a);
