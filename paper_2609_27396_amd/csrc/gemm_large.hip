@@ -251,23 +251,68 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
     if constexpr (EPI == EPI_TOP2) {
       static_assert(WN == 128, "one 128-column top-2 tile per wave column");
       const int tile = nt * WNW + wn, n_tiles = (a.N + 127) / 128;
+      // The values alone first: the largest three, v1 >= v2 >= v3, by a max and two medians a value,
+      // then the columns of v1 and v2 by comparing with them.  Two equal values among the three, a
+      // value that is not finite or columns past N: by keys (1088 rows x 151936 x 4096, keys for every
+      // value 1270 us, so 1137).
       Top3 t{};
+      float v1 = -INFINITY, v2 = -INFINITY, v3 = -INFINITY, zero = 0.f;
 #pragma unroll
-      for (int ni = 0; ni < FN; ++ni) {
-        __builtin_amdgcn_sched_barrier(0);
+      for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int col = nt * BN + wn * WN + ni * 16 + lc * 4 + r;
-          if (col < a.N) t.add(argmax_key(acc[mi][ni][r], (uint32_t)col));
+          const float x = acc[mi][ni][r];
+          zero = fmaf(x, 0.f, zero);
+          v3 = __builtin_amdgcn_fmed3f(v2, v3, x);
+          v2 = __builtin_amdgcn_fmed3f(v1, v2, x);
+          v1 = fmaxf(v1, x);
         }
-      }
 #pragma unroll
       for (int o = 16; o <= 32; o *= 2) {
-        Top3 u;
-        u.k1 = __shfl_xor((unsigned long long)t.k1, o, 64);
-        u.k2 = __shfl_xor((unsigned long long)t.k2, o, 64);
-        u.v3 = __shfl_xor(t.v3, o, 64);
-        t = Top3::merge(t, u);
+        const float u1 = __shfl_xor(v1, o, 64), u2 = __shfl_xor(v2, o, 64), u3 = __shfl_xor(v3, o, 64);
+        for (const float x : {u1, u2, u3}) {
+          v3 = __builtin_amdgcn_fmed3f(v2, v3, x);
+          v2 = __builtin_amdgcn_fmed3f(v1, v2, x);
+          v1 = fmaxf(v1, x);
+        }
+      }
+      if (__any(row < m_end && (zero != 0.f || v1 == v2 || v2 == v3)) || (tile + 1) * 128 > a.N) {
+#pragma unroll
+        for (int ni = 0; ni < FN; ++ni) {
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int col = nt * BN + wn * WN + ni * 16 + lc * 4 + r;
+            if (col < a.N) t.add(argmax_key(acc[mi][ni][r], (uint32_t)col));
+          }
+        }
+#pragma unroll
+        for (int o = 16; o <= 32; o *= 2) {
+          Top3 u;
+          u.k1 = __shfl_xor((unsigned long long)t.k1, o, 64);
+          u.k2 = __shfl_xor((unsigned long long)t.k2, o, 64);
+          u.v3 = __shfl_xor(t.v3, o, 64);
+          t = Top3::merge(t, u);
+        }
+      } else {
+        int c1 = -1, c2 = -1;
+#pragma unroll
+        for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            c1 = acc[mi][ni][r] == v1 ? ni * 16 + r : c1;
+            c2 = acc[mi][ni][r] == v2 ? ni * 16 + r : c2;
+          }
+        c1 = c1 < 0 ? -1 : c1 + lc * 4;
+        c2 = c2 < 0 ? -1 : c2 + lc * 4;
+#pragma unroll
+        for (int o = 16; o <= 32; o *= 2) {
+          c1 = max(c1, __shfl_xor(c1, o, 64));
+          c2 = max(c2, __shfl_xor(c2, o, 64));
+        }
+        t.k1 = argmax_key(v1, (uint32_t)(tile * 128 + c1));
+        t.k2 = argmax_key(v2, (uint32_t)(tile * 128 + c2));
+        t.v3 = v3;
       }
       if (lc == 0 && row < m_end && tile < n_tiles) {
         uint64_t* o = (uint64_t*)a.C + ((int64_t)row * a.ldc + tile) * 3;
