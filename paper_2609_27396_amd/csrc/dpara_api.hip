@@ -146,6 +146,11 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
     const int max_s = min(max_blocks / 2, kMaxAttnSplits);
     if (S > max_s) S = max_s;
     if (S < 1) S = 1;
+    // Between half and all of the CUs: a split of two lets the short halves of mixed contexts fill
+    // in behind the long ones (a layer of 3 requests, contexts 700-3000: 480 -> 473 us; 911-4084:
+    // 481 -> 445; equal contexts of 2752: 548 -> 541).  Not for short contexts (144 and 555 keys:
+    // 382 -> 386, 383 -> 389) and not at one workgroup per CU (2322 keys: 507 -> 509).
+    if (base > DPARA_ATTN_TARGET_WG / 2 && base < DPARA_ATTN_TARGET_WG && ctx_cap >= 2048) S = 2;
     if (base > DPARA_ATTN_TARGET_WG && max_s >= 2) {
       // Large batches: two workgroups fit on a CU (512 at once).  When the workgroups make at
       // most two rounds and the last one is at most 70% full, a split of two fills the rounds
