@@ -617,16 +617,22 @@ int dpara_ctx_append(const dpara_config_t* cfg, const dpara_weights_t* w, const 
     return DPARA_OK;
   }
   const int CH = n_max < p.CH ? n_max : p.CH;  // rows per request per chunk
+  // One chunk: the features are the GEMM's operand as they are, and the last store updates the
+  // lengths (the stores then read the first positions that the table's launch kept), so a round's
+  // update is a copy and a launch less: Qwen3-8B, batch 1, 59 -> 55 us.
+  const bool whole = CH == n_max;
+  int* pos0 = whole ? at<int>(ws, p.F) : nullptr;
   for (int c0 = 0; c0 < n_max; c0 += CH) {
-    HIP_TRY(launch_gather_feats(dt, batch, CH, c0, n_max, H, feats, at<void>(ws, p.F), st), "gather_feats");
-    HIP_TRY(launch_rope_table(batch, CH, hd, cfg->rope_base, ctx->ctx_len, c0, at<float2>(ws, p.rope_app), st),
+    if (!whole)
+      HIP_TRY(launch_gather_feats(dt, batch, CH, c0, n_max, H, feats, at<void>(ws, p.F), st), "gather_feats");
+    HIP_TRY(launch_rope_table(batch, CH, hd, cfg->rope_base, ctx->ctx_len, c0, at<float2>(ws, p.rope_app), st, pos0),
             "rope_table");
     // All layers project the same features: up to kMaxAppendLayers layers share one K|V GEMM
     // (weight segments W_k, W_v of each layer) and one store launch.
     for (int l0 = 0; l0 < cfg->n_layers; l0 += kMaxAppendLayers) {
       const int nl = cfg->n_layers - l0 < kMaxAppendLayers ? cfg->n_layers - l0 : kMaxAppendLayers;
       GemmArgs g{};
-      g.A = at<void>(ws, p.F);
+      g.A = whole ? feats : at<void>(ws, p.F);
       g.lda = H;
       g.seg_rows = nkv * hd;
       KvLayers kn{};
@@ -652,12 +658,14 @@ int dpara_ctx_append(const dpara_config_t* cfg, const dpara_weights_t* w, const 
       Phase ph("append_store", st);
       HIP_TRY(launch_kv_store(dt, batch, CH, c0, n_max, nkv, hd, cfg->qk_norm, cfg->rms_eps,
                               at<float2>(ws, p.rope_app), at<float>(ws, p.KV32), g.splits, nl, kn, n_new,
-                              ctx->ctx_len, ctx->ctx_cap, (char*)ctx->k + l0 * layer_elems * esz,
-                              (char*)ctx->v + l0 * layer_elems * esz, layer_elems, status, st),
+                              whole ? pos0 : ctx->ctx_len, ctx->ctx_cap, (char*)ctx->k + l0 * layer_elems * esz,
+                              (char*)ctx->v + l0 * layer_elems * esz, layer_elems,
+                              whole && l0 + nl == cfg->n_layers ? ctx->ctx_len : nullptr, status, st),
               "kv_store");
     }
   }
-  HIP_TRY(launch_ctx_len_update(batch, n_max, ctx->ctx_cap, n_new, ctx->ctx_len, status, st), "ctx_len_update");
+  if (!whole)
+    HIP_TRY(launch_ctx_len_update(batch, n_max, ctx->ctx_cap, n_new, ctx->ctx_len, status, st), "ctx_len_update");
   return DPARA_OK;
 }
 

@@ -124,8 +124,10 @@ __device__ __forceinline__ void rope_entry(int b, int idx, int n_pos, int hd, do
   table[((int64_t)b * n_pos + i) * half + p] = make_float2(c, s);
 }
 
+// pos0, if not NULL: the requests' first positions.
 __global__ void rope_table_kernel(int n_pos, int hd, double base, const int* ctx_len, int pos_off,
-                                  float2* table) {
+                                  float2* table, int* pos0) {
+  if (pos0 && blockIdx.x == 0 && threadIdx.x == 0) pos0[blockIdx.y] = max(ctx_len[blockIdx.y], 0) + pos_off;
   rope_entry(blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x, n_pos, hd, base, ctx_len, pos_off, table);
 }
 
@@ -251,16 +253,27 @@ __global__ __launch_bounds__(256) void gather_feats(int CH, int c0, int n_max, i
 
 __device__ __forceinline__ int clamp_count(int n, int n_max) { return n < 0 ? 0 : (n > n_max ? n_max : n); }
 
+// ctx_len[b] after n_new[b] rows at most n_max are appended to L positions.
+__device__ __forceinline__ int appended_len(int L, int raw, int n_max, int cap, int* status) {
+  const int n = clamp_count(raw, n_max);
+  if (n != raw) raise_status(status, 8);
+  if (L + n > cap) raise_status(status, 2);
+  return min(L + n, cap);
+}
+
 // K/V of appended rows: k = RoPE(kNorm(W_k f)) at its position, v = W_v f; K rows go to
-// [pos][hd], V to the transposed cache [hd][pos].
+// [pos][hd], V to the transposed cache [hd][pos].  ctx_len: the lengths before the append; len_out
+// (NULL: another launch does it) gets those after it.
 // Grid (kv-head groups of 4, rows, layers).
 template <typename T>
 __global__ __launch_bounds__(256) void kv_store(int CH, int c0, int n_max, int n_kv, int hd, int qk_norm, float eps,
                                                 const float2* rope, const float* KV, int S, int64_t pstride,
                                                 KvLayers kls, const int* n_new, const int* ctx_len, int cap,
-                                                T* Kc, T* Vc, int64_t layer_elems) {
+                                                T* Kc, T* Vc, int64_t layer_elems, int* len_out, int* status) {
   const int m = blockIdx.y, b = m / CH, i = m % CH, l = blockIdx.z, nl = gridDim.z;
   const int c = c0 + i;
+  if (len_out && i == 0 && l == 0 && blockIdx.x == 0 && threadIdx.x == 0)
+    len_out[b] = appended_len(max(ctx_len[b], 0), n_new[b], n_max, cap, status);
   if (c >= clamp_count(n_new[b], n_max)) return;
   const int pos = max(ctx_len[b], 0) + c;
   if (pos >= cap) return;
@@ -342,15 +355,7 @@ __global__ __launch_bounds__(256) void emit_hidden(int H, const float* X, const 
 __global__ void ctx_len_update_kernel(int B, int n_max, int cap, const int* n_new, int* ctx_len, int* status) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
-  const int raw = n_new[b];
-  const int n = clamp_count(raw, n_max);
-  if (n != raw) raise_status(status, 8);
-  int L = max(ctx_len[b], 0) + n;
-  if (L > cap) {
-    raise_status(status, 2);
-    L = cap;
-  }
-  ctx_len[b] = L;
+  ctx_len[b] = appended_len(max(ctx_len[b], 0), n_new[b], n_max, cap, status);
 }
 
 __global__ void clear_status_kernel(int* status) { status[threadIdx.x] = 0; }
@@ -431,11 +436,11 @@ hipError_t launch_assemble_rows_rope(int dtype, int B, int R, int gamma, int H, 
 }
 
 hipError_t launch_rope_table(int B, int n_pos, int hd, float base, const int* ctx_len, int pos_off,
-                             float2* table, hipStream_t st) {
+                             float2* table, hipStream_t st, int* pos0) {
   const int n = n_pos * (hd / 2);
   dim3 grid((n + 255) / 256, B);
   hipLaunchKernelGGL(rope_table_kernel, grid, dim3(256), 0, st, n_pos, hd, (double)base, ctx_len, pos_off,
-                     table);
+                     table, pos0);
   return hipGetLastError();
 }
 
@@ -478,19 +483,18 @@ hipError_t launch_gather_feats(int dtype, int B, int CH, int c0, int n_max, int 
 hipError_t launch_kv_store(int dtype, int B, int CH, int c0, int n_max, int n_kv, int hd, int qk_norm,
                            float eps, const float2* rope, const float* KV, int S, int nl, const KvLayers& kn,
                            const int* n_new, const int* ctx_len, int cap, void* Kc, void* Vc, size_t layer_elems,
-                           int* status, hipStream_t st) {
-  (void)status;
+                           int* len_out, int* status, hipStream_t st) {
   if (S < 1 || S > kMaxPlanes || nl < 1 || nl > kMaxAppendLayers) return hipErrorInvalidValue;
   const int64_t pstride = (int64_t)B * CH * nl * 2 * n_kv * hd;
   const dim3 grid((n_kv + 3) / 4, B * CH, nl);
   if (dtype == 1)
     hipLaunchKernelGGL(kv_store<bf16_t>, grid, dim3(256), 0, st, CH, c0, n_max, n_kv, hd, qk_norm, eps,
                        rope, KV, S, pstride, kn, n_new, ctx_len, cap, (bf16_t*)Kc, (bf16_t*)Vc,
-                       (int64_t)layer_elems);
+                       (int64_t)layer_elems, len_out, status);
   else
     hipLaunchKernelGGL(kv_store<float>, grid, dim3(256), 0, st, CH, c0, n_max, n_kv, hd, qk_norm, eps,
                        rope, KV, S, pstride, kn, n_new, ctx_len, cap, (float*)Kc, (float*)Vc,
-                       (int64_t)layer_elems);
+                       (int64_t)layer_elems, len_out, status);
   return hipGetLastError();
 }
 

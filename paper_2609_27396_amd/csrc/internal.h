@@ -157,7 +157,7 @@ hipError_t launch_assemble_rows_rope(int dtype, int B, int R, int gamma, int H, 
                                      const void* embed, const void* mask_emb, float* X, int* status, int n_pos,
                                      int hd, float base, const int* ctx_len, float2* table, hipStream_t st);
 hipError_t launch_rope_table(int B, int n_pos, int hd, float base, const int* ctx_len,
-                             int pos_off, float2* table, hipStream_t st);
+                             int pos_off, float2* table, hipStream_t st, int* pos0 = nullptr);
 // QKV: S fp32 planes [S][B*R][(n_q+2n_kv)*hd], summed in order.
 hipError_t launch_qk_norm_rope(int dtype, int B, int R, int Rp, int gamma, int n_q, int n_kv, int hd,
                                int qk_norm, float eps, const float* QKV, int S, const float* qn,
@@ -180,7 +180,7 @@ struct KvLayers {
 hipError_t launch_kv_store(int dtype, int B, int CH, int c0, int n_max, int n_kv, int hd,
                            int qk_norm, float eps, const float2* rope, const float* KV, int S,
                            int nl, const KvLayers& kn, const int* n_new, const int* ctx_len, int cap,
-                           void* Kc, void* Vc, size_t layer_elems, int* status, hipStream_t st);
+                           void* Kc, void* Vc, size_t layer_elems, int* len_out, int* status, hipStream_t st);
 // out[m * n_out + j][0..H) = X[m] + sum_{s<S} P[s][m] for rows m < rows, rounded to bf16
 // (out_f32 == 0) or kept float32.
 hipError_t launch_emit_hidden(int rows, int H, const float* X, const float* P, int S, int64_t pstride, void* out,
