@@ -643,6 +643,7 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st) {
     return run_pipe<128, 128, 4, 2, 3, 128, EPI_STORE_F32, 1>(a, st);
   }
   if (amode == A_BF16 && epi == EPI_TOP2 && a.ldc < (a.N + 127) / 128) return hipErrorInvalidValue;
+  if (epi == EPI_SCORE) return amode == A_BF16 ? launch_gemm_mid(epi, a, st) : hipErrorInvalidValue;
   if (amode == A_BF16 && gemm_mid_supported(epi, a)) return launch_gemm_mid(epi, a, st);
   if (amode == A_BF16 && gemm_large_supported(epi, a)) {
     if (epi == EPI_QKV && (a.N != (a.qkv.n_q + 2 * a.qkv.n_kv) * 128 || a.qkv.n_kv < 1 || a.qkv.n_q % a.qkv.n_kv ||

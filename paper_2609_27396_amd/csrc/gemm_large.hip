@@ -335,11 +335,25 @@ __device__ __forceinline__ void large_epilogue(const GemmArgs& a, f32x4_t (&acc)
         *(uint2*)(c + ni * 16) = pack4(v[0], v[1], v[2], v[3]);
       }
     } else {
-      const bool vec = ((a.N | (int)a.ldc) & 3) == 0;  // four columns are one aligned store
+      bool vec = ((a.N | (int)a.ldc) & 3) == 0;  // four columns are one aligned store
+      if constexpr (EPI == EPI_SCORE) vec = vec && (((uintptr_t)a.C | (uintptr_t)a.base) & 15) == 0;
       const int c0 = nt * BN + wn * WN + lc * 4;
 #pragma unroll
       for (int ni = 0; ni < FN; ++ni) {
-        const f32x4_t v = acc[mi][ni];
+        f32x4_t v = acc[mi][ni];
+        if constexpr (EPI == EPI_SCORE) {
+          const float* l = a.base + (int64_t)row * a.ldc + c0 + ni * 16;
+          f32x4_t x{0.f, 0.f, 0.f, 0.f};
+          if (vec) {
+            if (c0 + ni * 16 < a.N) x = *(const f32x4_t*)l;
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (c0 + ni * 16 + r < a.N) x[r] = l[r];
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = (x[r] + v[r]) * a.scale;
+        }
         if constexpr (EPI == EPI_STORE_BF16) {
           bf16_t* c = (bf16_t*)a.C + (int64_t)row * a.ldc + c0;
           if (vec) {
@@ -822,14 +836,19 @@ hipError_t pick_mid(const GemmArgs& a, hipStream_t st) {
     if (a.M <= 256) return run_mid<256, 256, 4, 2, 2, 3, EPI, 1>(a, st);
     return run_mid<160, 256, 2, 2, 2, 3, EPI, 0>(a, st);
   } else {
-    if (a.N > 32768) {  // (S == 1: a vocabulary's columns)
+    if (EPI == EPI_SCORE || a.N > 32768) {  // (S == 1: a vocabulary's columns)
+      if constexpr (EPI == EPI_SCORE)
+        if (a.M <= 64) return run_mid<64, 320, 4, 2, 2, 3, EPI, 1>(a, st);
       if (a.M <= 128) return run_mid<128, 320, 4, 2, 2, 3, EPI, 1>(a, st);
       if (a.M <= 192) return run_mid<192, 256, 4, 2, 2, 3, EPI, 1>(a, st);
       if (a.M <= 256) return run_mid<256, 192, 4, 2, 2, 3, EPI, 1>(a, st);
       return run_mid<160, 256, 2, 2, 2, 3, EPI, 0>(a, st);
     }
-    if (a.M <= 128) return run_mid<128, 128, 4, 2, 3, 3, EPI, 1>(a, st);
-    return run_mid<192, 128, 4, 2, 3, 3, EPI, 1>(a, st);
+    if constexpr (EPI != EPI_SCORE) {
+      if (a.M <= 128) return run_mid<128, 128, 4, 2, 3, 3, EPI, 1>(a, st);
+      return run_mid<192, 128, 4, 2, 3, 3, EPI, 1>(a, st);
+    }
+    return hipErrorInvalidValue;
   }
 }
 
@@ -856,6 +875,7 @@ int gemm_mid_splits(int N, int K) {
 }
 
 hipError_t launch_gemm_mid(int epi, const GemmArgs& a, hipStream_t st) {
+  if (epi == EPI_SCORE) return gemm_score_supported(a) ? pick_mid<EPI_SCORE>(a, st) : hipErrorInvalidValue;
   if (!gemm_mid_supported(epi, a)) return hipErrorInvalidValue;
   switch (epi) {
     case EPI_SWIGLU: return pick_mid<EPI_SWIGLU>(a, st);
@@ -863,6 +883,10 @@ hipError_t launch_gemm_mid(int epi, const GemmArgs& a, hipStream_t st) {
     case EPI_STORE_BF16: return pick_mid<EPI_STORE_BF16>(a, st);
     default: return pick_mid<EPI_TOP2>(a, st);
   }
+}
+
+bool gemm_score_supported(const GemmArgs& a) {
+  return a.M <= 320 && a.K % 128 == 0 && a.K >= 256 && a.lda == a.K && a.splits == 1 && a.seg_rows == 0 && a.n1 >= a.N;
 }
 
 bool gemm_dual_supported(const GemmArgs& a) {

@@ -22,7 +22,7 @@ struct Phase {
 // C[M, N] (op)= A[M, K] . B[N, K]^T with B given in up to three row segments
 // (rows [0, n1) from B0, [n1, n2) from B1, [n2, N) from B2), or, with seg_rows > 0 (not for
 // EPI_SWIGLU), in equal segments: row n from seg[n / seg_rows], row n % seg_rows.
-enum GemmEpi { EPI_STORE_F32 = 0, EPI_ADD_F32 = 1, EPI_SWIGLU = 2, EPI_STORE_BF16 = 3, EPI_TOP2 = 4, EPI_QKV = 5, EPI_KV = 6 };
+enum GemmEpi { EPI_STORE_F32 = 0, EPI_ADD_F32 = 1, EPI_SWIGLU = 2, EPI_STORE_BF16 = 3, EPI_TOP2 = 4, EPI_QKV = 5, EPI_KV = 6, EPI_SCORE = 7 };
 
 // Parameters of the EPI_QKV epilogue: the Q|K|V projection of R rows per request written as
 // the attention kernel's bf16 operands (Q [B, n_kv, grp * R, 128], in-block K [B, n_kv, Rp, 128],
@@ -94,6 +94,9 @@ struct GemmArgs {
   const void* seg[16] = {};
   QkvEpi qkv{};  // EPI_QKV only (bf16, head_dim 128, gemm_large_supported(), no split-K)
   KvEpi kv{};    // EPI_KV only (the same)
+  // EPI_SCORE (gemm_score_supported()): C = (base + A . B^T) * scale in float32, base [M, ldc] like C
+  const float* base = nullptr;
+  float scale = 1.f;
 };
 
 constexpr int kMaxGemmSegs = 16;
@@ -103,6 +106,8 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st);
 bool gemm_mid_supported(int epi, const GemmArgs& a);
 hipError_t launch_gemm_mid(int epi, const GemmArgs& a, hipStream_t st);
 int gemm_mid_splits(int N, int K);
+// The float32 score of head steps (EPI_SCORE) over at most 320 rows.
+bool gemm_score_supported(const GemmArgs& a);
 // The same for an A of two planes (A_BF16_DUAL, float32 store) over more than 32 rows.
 bool gemm_dual_supported(const GemmArgs& a);
 hipError_t launch_gemm_dual(const GemmArgs& a, hipStream_t st);

@@ -152,3 +152,36 @@ def test_prompt_append_is_its_short_appends(layers, starts, counts, n_max, cap, 
         assert torch.equal(a == mark, b == mark)
         a, b = a.float(), b.float()
         assert bool(((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5).all())
+
+
+# batch * gamma rows: 15, 64 | 66, 128 | 135, 192 | 198, 256 | 260, 320
+@pytest.mark.parametrize("batch,gamma", [(3, 5), (16, 4), (11, 6), (16, 8), (15, 9), (16, 12), (18, 11), (16, 16), (20, 13),
+                                         (20, 16)])
+def test_sampled_scores_around_tile_edges(batch, gamma):
+    """Draft scores of the sampled head where every step is proven, rank 256, a vocabulary that is no
+    multiple of four: (h . E_v + E(y_prev) . W_v) / T against float64."""
+    from paper_2609_27396_amd import dpara as D
+    s = synth.DrafterShape(n_layers=1, hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn=256, vocab=3001,
+                           gamma=gamma, ar_rank=256, qk_norm=True, dtype="bf16")
+    _say("case sampled scores", batch * gamma)
+    w = synth.make_weights(s, seed=6, gain_jitter=0.1, ar_w_std=0.005, ar_e_std=0.02)
+    dd = D.DeviceDrafter(s, w)
+    ws = D.Workspace(dd.cfg, batch, 64)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(batch)
+    reps = torch.empty((batch, gamma + 1, gamma, s.hidden), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    rng = np.random.default_rng(gamma)
+    acc = torch.from_numpy(rng.integers(0, gamma + 1, batch).astype(np.int32)).cuda()
+    bon = torch.from_numpy(rng.integers(0, s.vocab, batch).astype(np.int32)).cuda()
+    drafts = torch.empty((batch, gamma), dtype=torch.int32, device="cuda")
+    nsp = torch.empty((batch, gamma + 1), dtype=torch.int32, device="cuda")
+    scores = torch.full((batch, gamma, s.vocab), float("nan"), dtype=torch.float32, device="cuda")
+    D.select_and_head_sampled(dd, reps, acc, bon, None, drafts, nsp, None, 0.7, 11, scores, ws)
+    torch.cuda.synchronize()
+    assert ws.status() == 0 and ws.head_fallback() == 0
+    bf = lambda x: torch.from_numpy(np.asarray(x, np.float32)).to(torch.bfloat16).double()  # noqa: E731
+    h = torch.stack([reps[b, int(acc[b])] for b in range(batch)]).cpu().double()
+    prev = nsp[:, :gamma].cpu().long()
+    ref = (h @ bf(w["embed"]).T + bf(w["ar_E"])[prev] @ bf(w["ar_W"]).T) / 0.7
+    # h as bf16 hi + lo parts: 2^-16 of the products' magnitudes (256 of about 0.8 * 0.016)
+    assert (scores.cpu().double() - ref).abs().max() <= 1e-3
