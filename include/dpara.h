@@ -139,7 +139,7 @@ typedef struct dpara_ctx {
   int32_t ctx_cap;
 } dpara_ctx_t;
 
-/* Bytes of workspace every call below needs for `batch` requests and a cache of
+/* Bytes of workspace every call below needs for up to `batch` requests and a cache of
  * `ctx_cap` positions (the same workspace serves all four calls).  0 on invalid input. */
 size_t dpara_workspace_bytes(const dpara_config_t* cfg, int32_t batch, int32_t ctx_cap);
 

@@ -232,6 +232,14 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
   return p;
 }
 
+// Bytes for up to B requests: the key splits and the split-K planes fall with the rows, so a smaller
+// batch's plan can be the larger one (16 requests of gamma 4: 414 MB, 18: 410).
+size_t plan_bytes(const dpara_config_t* c, int B, int ctx_cap, int R) {
+  size_t n = 0;
+  for (int b = 1; b <= B; ++b) n = std::max(n, make_plan(c, b, ctx_cap, R).total);
+  return n;
+}
+
 std::mutex g_dev_mu;
 int g_dev_ok[64];  // 0 unknown, 1 gfx950, -1 other
 
@@ -534,7 +542,7 @@ const char* dpara_last_error(void) { return g_err.c_str(); }
 
 size_t dpara_workspace_bytes(const dpara_config_t* cfg, int32_t batch, int32_t ctx_cap) {
   if (check_cfg(cfg) != DPARA_OK || batch < 1 || ctx_cap < 64 || ctx_cap % 64) return 0;
-  return make_plan(cfg, batch, ctx_cap).total;
+  return plan_bytes(cfg, batch, ctx_cap, 0);
 }
 
 int dpara_clear_status(void* ws, void* stream) {
@@ -716,7 +724,7 @@ size_t dpara_target_workspace_bytes(const dpara_config_t* cfg, int32_t batch, in
   dpara_config_t c = *cfg;
   c.ar_rank = 64;
   if (check_cfg(&c) != DPARA_OK || batch < 1 || ctx_cap < 64 || ctx_cap % 64) return 0;
-  return make_plan(&c, batch, ctx_cap, cfg->gamma + 1).total;
+  return plan_bytes(&c, batch, ctx_cap, cfg->gamma + 1);
 }
 
 int dpara_target_forward(const dpara_config_t* cfg, const dpara_target_weights_t* w, const dpara_ctx_t* ctx,

@@ -29,6 +29,15 @@ def test_library_loads_and_exports_every_declared_symbol():
     assert D.dpara_version() == 100
 
 
+@pytest.mark.parametrize("gamma", [4, 6, 11, 16])
+@pytest.mark.parametrize("size", [D.dpara_workspace_bytes, D.dpara_target_workspace_bytes])
+def test_workspace_serves_smaller_batches(gamma, size):
+    cfg = D.make_config(dataclasses.replace(synth.QWEN3_8B, gamma=gamma))
+    for cap in (64, 2048, 8192):
+        n = [size(cfg, b, cap) for b in range(1, 21)]
+        assert n == sorted(n), cap
+
+
 def test_workspace_bytes():
     cfg = D.make_config(synth.QWEN3_8B)
     a = D.dpara_workspace_bytes(cfg, 1, 2112)
