@@ -568,8 +568,9 @@ hipError_t run_pipe(const GemmArgs& a, hipStream_t st) {
 // Tile choice for the bf16 projections that gemm_mid_supported() and gemm_large_supported() leave
 // (measured on MI355X at Qwen3-8B N/K):
 //  M <= 64  : (the context append, up to gamma+1 rows per request) 64x128 tiles, 3-deep ring.
-//  65-320   : O and down above 192 rows, and any K that is no multiple of 128: one 320-row tile
-//             covers every row, so each weight tile is read once; 8 waves (80x64 each), a 2-deep
+//  65-320   : above 192 rows where two row tiles leave CUs idle (the context append of few layers),
+//             and any K that is no multiple of 128: one 320-row tile covers every row, so each
+//             weight tile is read once; 8 waves (80x64 each), a 2-deep
 //             ring of 64-wide K steps.  The fp32-store GEMMs split K so that about 256 workgroups
 //             run; their consumers add the S partial planes (gemm_splits).
 //  above    : a K that is no multiple of 128: 64-row tiles.
@@ -603,7 +604,9 @@ int gemm_splits(int amode, int epi, int M, int N, int K, int seg) {
     return S;
   }
   if (amode != A_BF16 || epi != EPI_STORE_F32) return 1;
-  if (M > 64 && M <= 192 && N <= 32768 && K % 128 == 0 && K >= 256 && seg % 128 == 0) return gemm_mid_splits(N, K);
+  if (M > 64 && (M <= 192 || (M <= 320 && gemm_mid_two_tiles(N, K))) && N <= 32768 && K % 128 == 0 && K >= 256 &&
+      seg % 128 == 0)
+    return gemm_mid_splits(M, N, K);
   if (M > 320) return K % 128 == 0 && K >= 256 && seg % 256 == 0 ? gemm_large_splits(M, N, K) : 1;
   const int NT = (N + 127) / 128;
   const int max_wg = M <= 64 ? 512 : 256;  // the M <= 64 tile fits two workgroups per CU

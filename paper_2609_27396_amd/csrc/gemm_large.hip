@@ -815,7 +815,11 @@ hipError_t run_mid(const GemmArgs& a, hipStream_t st) {
 //             columns by four waves, so that Qwen3-8B gives 256 workgroups and the two that share
 //             a weight tile read it from one XCD's L2: 170 rows 54 (65), 238 59 (66), 289 63 (70).
 //  fp32     : up to 192 rows one row tile x 128 columns, K split over up to 256 workgroups: 102 rows
-//             down 25 (36), O 13 (17), Q|K|V 18 (24); 170 rows down 30, O 16, Q|K|V 21.
+//             down 25 (36), O 13 (17), Q|K|V 18 (24); 170 rows down 30, O 16, Q|K|V 21.  Above, two equal
+//             row tiles x 128 columns where these and K's splits give 7/8 of the CUs a workgroup: half
+//             the planes of the one 320-row tile, or workgroups on CUs it left idle (40 column tiles
+//             take three splits, not four).  Drafter of 225 and 289 rows, Qwen3-14B: 1745 and 1867 us,
+//             so 1639 and 1757; of 196 and 289 rows, Qwen3-8B: 989 and 1097, so 980 and 1084.
 //  LM head  : wide tiles, so that the last round is nearly full: 102 rows x 320 columns 228 (371),
 //             170 x 256 267, 238 x 192 340, 272 rows as two row tiles of 160 x 256 373 (382).
 //  top-2    : 128-column wave tiles: 128, 192, 256 (or two of 160) rows x 256 columns.
@@ -846,6 +850,8 @@ hipError_t pick_mid(const GemmArgs& a, hipStream_t st) {
     }
     if constexpr (EPI != EPI_SCORE) {
       if (a.M <= 128) return run_mid<128, 128, 4, 2, 3, 3, EPI, 1>(a, st);
+      if constexpr (EPI == EPI_STORE_F32)
+        if (a.M > 192) return run_mid<160, 128, 2, 2, 3, 3, EPI, 0>(a, st);
       return run_mid<192, 128, 4, 2, 3, 3, EPI, 1>(a, st);
     }
     return hipErrorInvalidValue;
@@ -864,11 +870,16 @@ bool gemm_mid_supported(int epi, const GemmArgs& a) {
   // a 128-column tile comes from one weight segment
   const bool segs = a.seg_rows > 0 ? a.seg_rows % 128 == 0
                                    : (a.n1 >= a.N || a.n1 % 128 == 0) && (a.n2 >= a.N || a.n2 % 128 == 0);
-  return a.M <= 192 && segs;
+  if (a.M <= 192) return segs;
+  return segs && epi == EPI_STORE_F32 && gemm_mid_two_tiles(a.N, a.K) && a.splits == gemm_mid_splits(a.M, a.N, a.K);
 }
 
-int gemm_mid_splits(int N, int K) {
-  int S = kCus / ((N + 127) / 128);
+bool gemm_mid_two_tiles(int N, int K) {
+  return 2 * ((N + 127) / 128) * gemm_mid_splits(320, N, K) >= kCus * 7 / 8;
+}
+
+int gemm_mid_splits(int M, int N, int K) {
+  int S = kCus / ((N + 127) / 128 * (M > 192 ? 2 : 1));
   if (S > 8) S = 8;  // the consumers' plane reads grow with S
   if (S > K / 256) S = K / 256;
   return S < 1 ? 1 : S;

@@ -102,10 +102,12 @@ struct GemmArgs {
 constexpr int kMaxGemmSegs = 16;
 hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st);
 // The streaming kernels for 65 to 320 bf16 rows (gemm_large.hip): whether they take this call,
-// its launch, and the split-K planes of its float32 store (at most 192 rows).
+// its launch, whether two row tiles fill the CUs at 193 to 320 rows, and the split-K planes of its
+// float32 store.
 bool gemm_mid_supported(int epi, const GemmArgs& a);
 hipError_t launch_gemm_mid(int epi, const GemmArgs& a, hipStream_t st);
-int gemm_mid_splits(int N, int K);
+bool gemm_mid_two_tiles(int N, int K);
+int gemm_mid_splits(int M, int N, int K);
 // The float32 score of head steps (EPI_SCORE) over at most 320 rows.
 bool gemm_score_supported(const GemmArgs& a);
 // The same for an A of two planes (A_BF16_DUAL, float32 store) over more than 32 rows.

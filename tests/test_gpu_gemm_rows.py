@@ -44,6 +44,24 @@ def test_fused_features_around_tile_edges(hidden):
         assert np.all(np.abs(out.float().cpu().numpy() - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-4), n
 
 
+# two row tiles over K split eight ways (29 units of 128, dealt unevenly); the last column tile is half full
+@pytest.mark.parametrize("n", [192, 193, 289, 319, 320, 321])
+def test_fused_features_of_two_row_tiles(n):
+    from paper_2609_27396_amd import dpara as D
+    s = _shape(1856, 256, 500, 4)
+    wf = synth.make_fusion_weights(s, n_feat=2, seed=31, gain_jitter=0.1)
+    fus = D.DeviceFusion(s, wf, 2)
+    _say("case fuse 1856", n)
+    hid = synth.make_target_hidden(s, n, n_feat=2, seed=32 + n)
+    out = torch.empty((n, s.hidden), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(D.dpara_fuse_workspace_bytes(fus.cfg, n, 2), dtype=torch.uint8, device="cuda")
+    D.fuse_features(fus, torch.from_numpy(hid).to(device="cuda", dtype=torch.bfloat16), out, ws)
+    torch.cuda.synchronize()
+    ref = O.fuse_features(s, wf, hid, "bf16")
+    # one bf16 rounding, and the float32 summation error of a 2H-term projection near zero
+    assert np.all(np.abs(out.float().cpu().numpy() - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-4), n
+
+
 # requests of 17 block rows: 68, 119 | 136, 187 | 204, 255 | 272, 306 | 323, 391 rows.  hidden 384 is
 # three 128-deep K steps; ffn 640 and vocab 3001 leave ragged column tiles at every tile width
 @pytest.mark.parametrize("batch", [4, 7, 8, 11, 12, 15, 16, 18, 19, 23])
