@@ -215,8 +215,8 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
   p.hwpart = take((size_t)head_prune_wparts() * 4);                // pruned head: |W_v|^2 maxima
   p.hflag = 4;  // pruned head: fallback flag, int32 in the header after the status word
   p.F = take((size_t)B * p.CH * H * p.esz);
-  // append K|V planes of one layer group: split only when the append GEMM has at most 320
-  // rows (16 planes max)
+  // append K|V planes of one layer group: 16 planes of 320 rows or one of a whole chunk (more rows
+  // split K as far as their planes fit)
   const int app_layers = c->n_layers < kMaxAppendLayers ? c->n_layers : kMaxAppendLayers;
   const size_t kv_rows = (size_t)B * p.CH > 16 * 320 ? (size_t)B * p.CH : 16 * 320;
   p.KV32 = take(kv_rows * app_layers * 2 * nkv * hd * 4);
