@@ -585,8 +585,10 @@ hipError_t run_bf16(const GemmArgs& a, hipStream_t st) {
   // activation rows, four waves of 16 rows, the empty row blocks skipped.  36-layer target at
   // batch 1: gate|up 54 -> 46 us per layer with 64-deep stages in a 6-deep ring, then 1.2% off
   // the whole target with the 128-deep stages.
+  // A K that is no multiple of 128 takes 64-deep stages.
   if constexpr (EPI == EPI_SWIGLU)
-    if (a.M <= 64) return run_pipe<64, 96, 4, 1, 3, 256, EPI>(a, st);
+    if (a.M <= 64)
+      return a.K % 128 == 0 ? run_pipe<64, 96, 4, 1, 3, 256, EPI>(a, st) : run_pipe<64, 128, 2, 2, 3, 128, EPI>(a, st);
   // SwiGLU: 48 gate + 48 up rows per tile
   if constexpr (EPI == EPI_SWIGLU) return run_pipe<320, 96, 4, 1, 2, 128, EPI>(a, st);
   return run_pipe<320, 128, 4, 2, 2, 128, EPI>(a, st);
@@ -636,12 +638,13 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st) {
     // for the whole batch-1 head: 64-deep stages at two workgroups per CU 280 us, 128-deep in a
     // 4-deep ring 266-270, 256-deep 256-258.  The per-32-deep-chunk order of the MFMAs (hi,
     // then lo) is unchanged.
-    if (a.M <= 16) return run_pipe<16, 128, 1, 4, 2, 512, EPI_STORE_F32, 1>(a, st);
+    if (a.M <= 16 && a.K % 256 == 0) return run_pipe<16, 128, 1, 4, 2, 512, EPI_STORE_F32, 1>(a, st);
     // 32 rows (two requests): the same 128-deep stages in a 3-deep ring, 15% faster than the
     // 64-row tile with half its rows idle (batch-2 head 325-345 -> 282 us on MI355X).
-    if (a.M <= 32) return run_pipe<32, 128, 1, 4, 3, 256, EPI_STORE_F32, 1>(a, st);
+    // (Also 16 rows with a K of 128-deep stages only.)
+    if (a.M <= 32 && a.K % 128 == 0) return run_pipe<32, 128, 1, 4, 3, 256, EPI_STORE_F32, 1>(a, st);
     if (epi == EPI_STORE_F32 && gemm_dual_supported(a)) return launch_gemm_dual(a, st);
-    // more rows with a K that is no multiple of 128 or weights in segments
+    // a K that is no multiple of 128 or weights in segments
     if (a.M <= 64) return run_pipe<64, 128, 2, 2, 3, 128, EPI_STORE_F32, 1>(a, st);
     return run_pipe<128, 128, 4, 2, 3, 128, EPI_STORE_F32, 1>(a, st);
   }

@@ -203,3 +203,24 @@ def test_sampled_scores_around_tile_edges(batch, gamma):
     ref = (h @ bf(w["embed"]).T + bf(w["ar_E"])[prev] @ bf(w["ar_W"]).T) / 0.7
     # h as bf16 hi + lo parts: 2^-16 of the products' magnitudes (256 of about 0.8 * 0.016)
     assert (scores.cpu().double() - ref).abs().max() <= 1e-3
+
+
+# hidden and ffn that are multiples of 64 but not of the K stages of the kernels for few rows: the
+# gate/up product of at most 64 rows takes 128-deep stages, the two-plane head 256-deep ones up to
+# 16 rows and 128-deep ones up to 32.  Block rows 25, 50 | 147, head rows 4, 8 | 18
+@pytest.mark.parametrize("hidden,ffn,gamma,ctx", [(64, 64, 4, [20]), (128, 320, 4, [20, 0]), (320, 576, 4, [70]),
+                                                  (320, 320, 6, [0, 77, 30]), (384, 640, 4, [70, 5])])
+def test_rounds_of_every_hidden_multiple_of_64(hidden, ffn, gamma, ctx):
+    from test_gpu_parity import check_head, check_verify, run_full
+    s = synth.DrafterShape(n_layers=2, hidden=hidden, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn=ffn, vocab=3001,
+                           gamma=gamma, ar_rank=64, qk_norm=True, dtype="bf16")
+    _say("case round", hidden, ffn, gamma, ctx)
+    wl = synth.Workload("multiple_of_64", s, batch=len(ctx), ctx_min=0, ctx_max=0, p_reject=0.3, seed_in=7)
+    w = synth.make_weights(s, seed=3, gain_jitter=0.1, ar_e_std=1.0)
+    ri = synth.make_round(wl, ctx_lens=ctx)
+    dr = run_full(wl, w, ri)
+    check_verify(ri, dr)
+    for b in range(len(ctx)):
+        ref = O.backbone_all_boundaries(s, w, ri.ctx_feats[b], ri.spine[b], "bf16")["reps"]
+        assert np.abs(dr.reps[b].cpu().numpy() - ref).max() <= TOL, b
+        check_head(s, w, dr, "bf16", b)
