@@ -253,6 +253,83 @@ __global__ __launch_bounds__(64 * WMW * WNW) void gemm_pipe_kernel(GemmArgs a, i
     }
   }
 
+  if constexpr (EPI == EPI_QKV) {
+    // One 128-wide head per wave column: the row's sum of squares over the head is this
+    // lane's eight columns plus the 16 lanes sharing the row (DPP), and RoPE's rotate-half
+    // partner of column d (d +- 64) is fragment ni +- 4 of the same lane.  Same arithmetic as
+    // the q/k-norm kernel: y = x * (1 / sqrt(ss / 128 + eps)) * g, then
+    // y_d = y_d cos - y_{d+64} sin, y_{d+64} = y_{d+64} cos + y_d sin.  The bf16 results go
+    // through this wave's part of the (now free) LDS ring, [WM rows][128 + 8 columns], so that
+    // Q and K leave as 16-byte row pieces and V^T as 64 consecutive rows per store (the launch
+    // sizes the dynamic LDS for this staging: up to 139 KB against the 128 KB ring).
+    static_assert(WN == 128 && FN == 8 && WM <= 64 && DUAL == 0, "one 128-wide head per wave column");
+    constexpr int LDT = 136;  // staging row stride in bf16 (272 bytes: rows fall on different banks)
+    const QkvEpi& e = a.qkv;
+    const int slot = nt * (BN / 128) + wn;
+    const int grp = e.n_q / e.n_kv;
+    const bool live = slot < e.n_q + 2 * e.n_kv;
+    const bool isv = slot >= e.n_q + e.n_kv, isq = slot < e.n_q;
+    bf16_t* stg = (bf16_t*)smem + wave * WM * LDT;
+    __syncthreads();  // every wave is done with the ring
+    if (!live) return;  // past the last head (no barrier follows)
+    const float* gain = isq ? e.qn : e.kn;
+    const int row0 = m0 + wm * WM;  // this wave's first row
+#pragma unroll
+    for (int mi = 0; mi < FM; ++mi) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int lrow = mi * 16 + lc * 4 + r, row = row0 + lrow;
+        float v[FN];
+#pragma unroll
+        for (int ni = 0; ni < FN; ++ni) v[ni] = acc[mi][ni][r];
+        if (!isv) {
+          if (e.qk_norm) {
+            float ss = 0.f;
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni) ss += v[ni] * v[ni];
+            ss = row16_sum(ss);
+            const float rn = 1.0f / sqrtf(ss / 128.0f + e.eps);
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni) v[ni] = v[ni] * rn * gain[ni * 16 + lr];
+          }
+          const int rc = min(row, a.M - 1), b = rc / e.R;
+          const float2* cs = e.table + ((int64_t)b * (2 * e.gamma + 1) + row_pos_offset(rc - b * e.R, e.gamma)) * 64 + lr;
+#pragma unroll
+          for (int ni = 0; ni < FN / 2; ++ni) {
+            const float2 c = cs[ni * 16];
+            const float lo = v[ni], hi = v[ni + 4];
+            v[ni] = lo * c.x + -1.f * hi * c.y;
+            v[ni + 4] = hi * c.x + 1.f * lo * c.y;
+          }
+        }
+#pragma unroll
+        for (int ni = 0; ni < FN; ++ni) stg[lrow * LDT + ni * 16 + lr] = f2bf(v[ni]);
+      }
+    }
+    if (!isv) {
+      // row pieces: lane (rq, piece) stores 16 bytes = columns 8 piece .. +7 of rows rq, rq+4, ...
+      const int piece = lane & 15;
+#pragma unroll 4
+      for (int lrow = lane >> 4; lrow < WM; lrow += 4) {
+        const int row = row0 + lrow;
+        if (row >= a.M) break;
+        const int b = row / e.R, rr = row - b * e.R;
+        bf16_t* dst = isq ? (bf16_t*)e.Q + (((int64_t)(b * e.n_kv + slot / grp) * grp + slot % grp) * e.R + rr) * 128
+                          : (bf16_t*)e.Kb + ((int64_t)(b * e.n_kv + (slot - e.n_q)) * e.Rp + rr) * 128;
+        *(uint4*)(dst + piece * 8) = *(const uint4*)(stg + lrow * LDT + piece * 8);
+      }
+    } else {
+      // V^T [128][Rp]: lane = row, one store per head dimension (WM consecutive rows of a
+      // request, split where a request ends)
+      const int row = row0 + lane;
+      if (lane < WM && row < a.M) {
+        const int b = row / e.R, rr = row - b * e.R;
+        bf16_t* dst = (bf16_t*)e.Vb + (int64_t)(b * e.n_kv + (slot - e.n_q - e.n_kv)) * 128 * e.Rp + rr;
+        for (int d = 0; d < 128; ++d) dst[(int64_t)d * e.Rp] = stg[lane * LDT + d];
+      }
+    }
+    return;
+  }
   if constexpr (EPI == EPI_TOP2) {
     // One (key1, key2, third value) triple per row and 128-column tile (WPT wave columns each):
     // per lane over its columns of each row (FN of them); then the 16 lanes that share the
@@ -552,7 +629,8 @@ hipError_t run_pipe(const GemmArgs& a, hipStream_t st) {
   const int MT = (a.M + BM - 1) / BM;
   const int NT = EPI == EPI_SWIGLU ? (a.N + BN / 2 - 1) / (BN / 2) : (a.N + BN - 1) / BN;
   constexpr int ring = STAGES * ((DUAL ? 2 : 1) * BM + BN) * BKB;
-  constexpr int lds = ring;
+  constexpr int stage_out = EPI == EPI_QKV ? (BM / WMW) * WMW * WNW * 136 * 2 : 0;  // the QKV epilogue's staging
+  constexpr int lds = ring > stage_out ? ring : stage_out;
   static_assert(lds <= 163840, "LDS ring exceeds 160 KB");
   auto kern = gemm_pipe_kernel<BM, BN, WMW, WNW, STAGES, BKB, EPI, DUAL>;
   static const hipError_t attr =
@@ -573,9 +651,80 @@ hipError_t run_pipe(const GemmArgs& a, hipStream_t st) {
 //             weight tile is read once; 8 waves (80x64 each), a 2-deep
 //             ring of 64-wide K steps.  The fp32-store GEMMs split K so that about 256 workgroups
 //             run; their consumers add the S partial planes (gemm_splits).
-//  above    : a K that is no multiple of 128: 64-row tiles.
+//  above    : where a K that is no multiple of 128 or a weight segment that is no multiple of 256
+//             rows keeps the persistent kernel out: 64 x 128 tiles up to 1024 rows, above them
+//             256 x 256 (192 x 256 where these fill the rounds of the CUs better).
+// Fraction of the last round of workgroups that has work (one workgroup per CU) for
+// BM x 256 tiles: 192-row tiles are taken when they fill the rounds clearly better.
+double round_fill(int M, int N, int BM) {
+  const double w = (double)((M + BM - 1) / BM) * ((N + 255) / 256) / 256.0;
+  return w / ceil(w);
+}
+
+// More than 1024 rows of a product the persistent kernel does not take.  A drafter with hidden 2880
+// and ffn 8640, one layer of 1156, 2312 and 4624 rows: 435, 625 and 1073 us, with 64 x 128 tiles 500,
+// 836 and 1467.
+template <int EPI>
+hipError_t run_tall(const GemmArgs& a, hipStream_t st) {
+  if constexpr (EPI == EPI_STORE_F32) {
+    // Fewer than 192 tiles of 256 x 256 (under three quarters of one round, e.g. the
+    // 2048-row feature fusion, 4096 columns: 128 tiles): 128 x 128 tiles at two workgroups
+    // per CU fill the chip instead.
+    if (a.splits == 1 && (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256) < 192)
+      return run_pipe<128, 128, 2, 2, 2, 128, EPI>(a, st);
+    // One weight matrix, no split-K: when the last round of BM x 256 tiles is at most 60%
+    // full, the columns of that round go to a second launch of 128 x 128 tiles (two
+    // workgroups per CU) and the first runs whole rounds only.  Measured on MI355X at
+    // Qwen3-8B batch 16 (4624 rows, 400 tiles of 192 x 256 = 1.56 rounds): O 876 -> 858,
+    // down 2404 -> 2342 us per step.
+    const bool bm192 = round_fill(a.M, a.N, 192) > round_fill(a.M, a.N, 256) + 0.1;
+    const int BMc = bm192 ? 192 : 256;
+    const int MT = (a.M + BMc - 1) / BMc, NT = (a.N + 255) / 256, T = MT * NT;
+    const int NT1 = (T / 256) * 256 / MT;  // 256-column tiles of the whole rounds
+    if (a.splits == 1 && a.seg_rows == 0 && a.n1 >= a.N && T % 256 != 0 && T % 256 <= 256 * 6 / 10 && NT1 > 0 &&
+        NT1 < NT) {
+      GemmArgs head = a, tail = a;
+      const int n0 = NT1 * 256;
+      head.N = n0;
+      tail.B0 = tail.B1 = tail.B2 = (const bf16_t*)a.B0 + (int64_t)n0 * a.K;
+      tail.n1 = tail.n2 = a.N - n0;
+      tail.C = (float*)a.C + n0;
+      tail.N = a.N - n0;
+      const hipError_t e = bm192 ? run_pipe<192, 256, 2, 4, 2, 128, EPI>(head, st)
+                                 : run_pipe<256, 256, 2, 4, 2, 128, EPI>(head, st);
+      if (e != hipSuccess) return e;
+      return run_pipe<128, 128, 2, 2, 2, 128, EPI>(tail, st);
+    }
+  }
+  if (EPI != EPI_SWIGLU && round_fill(a.M, a.N, 192) > round_fill(a.M, a.N, 256) + 0.1)
+    return run_pipe<192, 256, 2, 4, 2, 128, EPI>(a, st);
+  if constexpr (EPI == EPI_SWIGLU) {
+    // When the 256 x 256 tiles leave a last round of workgroups at most half full, the FFN
+    // columns of that round go to a second launch of 128 x 128 tiles (64 gate + 64 up
+    // columns, two workgroups per CU), four times as many workgroups each a quarter of the
+    // work: the first launch runs whole rounds only.  Measured on MI355X: 4.3% off the
+    // Qwen3-14B batch-8 gate/up (5.3 rounds), 2.6% off Qwen3-8B batch 16 (7.1 rounds).
+    const int MT = (a.M + 255) / 256, NT = (a.N + 127) / 128, T = MT * NT;
+    const int NT1 = (T / 256) * 256 / MT;  // FFN column tiles of the whole rounds
+    if (T % 256 != 0 && T % 256 <= 128 && NT1 > 0 && NT1 < NT) {
+      GemmArgs head = a, tail = a;
+      head.N = NT1 * 128;
+      const int f0 = NT1 * 128;
+      tail.B0 = (const bf16_t*)a.B0 + (int64_t)f0 * a.K;
+      tail.B1 = (const bf16_t*)a.B1 + (int64_t)f0 * a.K;
+      tail.C = (bf16_t*)a.C + f0;
+      tail.N = a.N - f0;
+      const hipError_t e = run_pipe<256, 256, 2, 4, 2, 128, EPI>(head, st);
+      if (e != hipSuccess) return e;
+      return run_pipe<128, 128, 2, 2, 2, 128, EPI>(tail, st);
+    }
+  }
+  return run_pipe<256, 256, 2, 4, 2, 128, EPI>(a, st);
+}
+
 template <int EPI>
 hipError_t run_bf16(const GemmArgs& a, hipStream_t st) {
+  if (a.M > 1024) return run_tall<EPI>(a, st);
   // up to 32 rows (a 17-row verification, the context append, the sampled head's scores): a
   // 32-row tile halves the activation rows each stage loads (target at batch 1: -1.2%)
   if (a.M <= 32 && EPI != EPI_SWIGLU) return run_pipe<32, 128, 2, 2, 3, 128, EPI>(a, st);
@@ -646,22 +795,32 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st) {
     if (epi == EPI_STORE_F32 && gemm_dual_supported(a)) return launch_gemm_dual(a, st);
     // a K that is no multiple of 128 or weights in segments
     if (a.M <= 64) return run_pipe<64, 128, 2, 2, 3, 128, EPI_STORE_F32, 1>(a, st);
+    // 129-256 rows: one 256-row tile (both planes, 2-deep ring of 160 KB), so each weight tile is read
+    // once (hidden 2880, 144 rows: the sampled step 795 -> 605 us)
+    if (a.M > 128 && a.M <= 256) return run_pipe<256, 128, 4, 2, 2, 128, EPI_STORE_F32, 1>(a, st);
     return run_pipe<128, 128, 4, 2, 3, 128, EPI_STORE_F32, 1>(a, st);
   }
   if (amode == A_BF16 && epi == EPI_TOP2 && a.ldc < (a.N + 127) / 128) return hipErrorInvalidValue;
   if (epi == EPI_SCORE) return amode == A_BF16 ? launch_gemm_mid(epi, a, st) : hipErrorInvalidValue;
   if (amode == A_BF16 && gemm_mid_supported(epi, a)) return launch_gemm_mid(epi, a, st);
-  if (amode == A_BF16 && gemm_large_supported(epi, a)) {
-    if (epi == EPI_QKV && (a.N != (a.qkv.n_q + 2 * a.qkv.n_kv) * 128 || a.qkv.n_kv < 1 || a.qkv.n_q % a.qkv.n_kv ||
-                           a.qkv.R < 1 || a.qkv.Rp < a.qkv.R))
-      return hipErrorInvalidValue;
-    return launch_gemm_large(epi, a, st);
-  }
+  if (epi == EPI_QKV && (amode != A_BF16 || a.splits != 1 || a.N != (a.qkv.n_q + 2 * a.qkv.n_kv) * 128 ||
+                         a.qkv.n_kv < 1 || a.qkv.n_q % a.qkv.n_kv || a.qkv.R < 1 || a.qkv.Rp < a.qkv.R))
+    return hipErrorInvalidValue;
+  if (amode == A_BF16 && gemm_large_supported(epi, a)) return launch_gemm_large(epi, a, st);
   if (epi == EPI_TOP2) {  // at most 64 rows, or a K that is no multiple of 128
-    if (amode != A_BF16 || a.ldc < (a.N + 127) / 128) return hipErrorInvalidValue;
+    if (amode != A_BF16) return hipErrorInvalidValue;
+    // 193-256 rows in one row tile, and 256 x 256 tiles from 1537 rows on (hidden 2880, 2176 rows:
+    // candidates 2626 -> 2488 us); else 192 x 128 tiles
+    if ((a.M > 192 && a.M <= 256) || a.M > 1536) return run_pipe<256, 256, 2, 4, 2, 128, EPI_TOP2, 0>(a, st);
     return run_pipe<192, 128, 2, 2, 2, 128, EPI_TOP2, 0>(a, st);
   }
-  if (epi == EPI_QKV || epi == EPI_KV) return hipErrorInvalidValue;  // the large-M kernel's epilogues
+  if (epi == EPI_QKV) {  // the same shapes as run_tall, its row tiles
+    if (a.M <= 1024) return hipErrorInvalidValue;
+    if (round_fill(a.M, a.N, 192) > round_fill(a.M, a.N, 256) + 0.1)
+      return run_pipe<192, 256, 4, 2, 2, 128, EPI_QKV, 0>(a, st);
+    return run_pipe<256, 256, 4, 2, 2, 128, EPI_QKV, 0>(a, st);
+  }
+  if (epi == EPI_KV) return hipErrorInvalidValue;  // the large-M kernel's epilogue
   if (amode == A_BF16_FRAG) {
     return epi == EPI_STORE_F32 ? run_adir(a, st) : hipErrorInvalidValue;
   }

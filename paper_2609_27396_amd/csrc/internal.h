@@ -92,8 +92,8 @@ struct GemmArgs {
   const int* only_if = nullptr;  // non-NULL: every workgroup returns at once unless *only_if != 0
   int seg_rows = 0;               // > 0: B rows from seg[] (N <= kMaxGemmSegs * seg_rows)
   const void* seg[16] = {};
-  QkvEpi qkv{};  // EPI_QKV only (bf16, head_dim 128, gemm_large_supported(), no split-K)
-  KvEpi kv{};    // EPI_KV only (the same)
+  QkvEpi qkv{};  // EPI_QKV only (bf16, head_dim 128, gemm_large_supported() or above 1024 rows, no split-K)
+  KvEpi kv{};    // EPI_KV only (bf16, head_dim 128, gemm_large_supported(), no split-K)
   // EPI_SCORE (gemm_score_supported()): C = (base + A . B^T) * scale in float32, base [M, ldc] like C
   const float* base = nullptr;
   float scale = 1.f;

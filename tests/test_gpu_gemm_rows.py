@@ -90,13 +90,9 @@ def test_target_rows_around_tile_edges(batch):
     np.testing.assert_allclose(lb.float().cpu().numpy(), lf.cpu().numpy(), rtol=2 ** -8, atol=0)
 
 
-# branch rows batch * (gamma + 1) * gamma: 72, 126 | 144, 180 | 198, 252 | 270, 320 | 360
-@pytest.mark.parametrize("batch,gamma", [(6, 3), (3, 6), (2, 8), (9, 4), (1, 13), (6, 6), (3, 9), (16, 4), (4, 9)])
-def test_candidate_rows_around_tile_edges(batch, gamma):
-    """Candidates of every branch row, then the serial step: where every step is proven, bit for
-    bit the plain head (whose rows are at most 64 here and take another kernel)."""
+def candidates_are_the_plain_head(batch, gamma, hidden):
     from paper_2609_27396_amd import dpara as D
-    s = _shape(256, 256, 3000, gamma)
+    s = _shape(hidden, 256, 3000, gamma)
     _say("case candidate rows", batch * (gamma + 1) * gamma)
     w = synth.make_weights(s, seed=6, gain_jitter=0.1, ar_w_std=0.005, ar_e_std=0.02)
     dd = D.DeviceDrafter(s, w)
@@ -125,6 +121,14 @@ def test_candidate_rows_around_tile_edges(batch, gamma):
     assert ws.status() == 0 and ws.head_fallback() == 0
     for x, y in zip(a, b):
         assert torch.equal(x, y)
+
+
+# branch rows batch * (gamma + 1) * gamma: 72, 126 | 144, 180 | 198, 252 | 270, 320 | 360
+@pytest.mark.parametrize("batch,gamma", [(6, 3), (3, 6), (2, 8), (9, 4), (1, 13), (6, 6), (3, 9), (16, 4), (4, 9)])
+def test_candidate_rows_around_tile_edges(batch, gamma):
+    """Candidates of every branch row, then the serial step: where every step is proven, bit for
+    bit the plain head (whose rows are at most 64 here and take another kernel)."""
+    candidates_are_the_plain_head(batch, gamma, 256)
 
 
 # rows of one append: just above 320, row tiles of padding only, two layer groups, an append past the
@@ -224,3 +228,52 @@ def test_rounds_of_every_hidden_multiple_of_64(hidden, ffn, gamma, ctx):
         ref = O.backbone_all_boundaries(s, w, ri.ctx_feats[b], ri.spine[b], "bf16")["reps"]
         assert np.abs(dr.reps[b].cpu().numpy() - ref).max() <= TOL, b
         check_head(s, w, dr, "bf16", b)
+
+
+# more than 1024 rows of products the persistent kernel does not take (K = 64 mod 128): 128 x 128
+# tiles; whole rounds of 256 x 256 and a second launch for the last columns; 256 x 256; 192 x 256
+@pytest.mark.parametrize("hidden,n", [(320, 1025), (4160, 4096), (2880, 4096), (8128, 2400)])
+def test_fused_features_above_1024_rows(hidden, n):
+    from paper_2609_27396_amd import dpara as D
+    s = _shape(hidden, 256, 500, 4)
+    wf = synth.make_fusion_weights(s, n_feat=1, seed=41, gain_jitter=0.1)
+    fus = D.DeviceFusion(s, wf, 1)
+    _say("case fuse above 1024", hidden, n)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(hidden)
+    hid = torch.empty((n, hidden), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    out = torch.empty((n, hidden), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(D.dpara_fuse_workspace_bytes(fus.cfg, n, 1), dtype=torch.uint8, device="cuda")
+    D.fuse_features(fus, hid, out, ws)
+    x = hid.double() @ torch.from_numpy(wf["fc"]).cuda().double().T
+    ref = x / torch.sqrt((x * x).mean(-1, keepdim=True) + s.rms_eps) * torch.from_numpy(wf["fc_norm"]).cuda().double()
+    assert bool(((out.double() - ref).abs() <= 2.0 ** -7 * ref.abs() + 1e-4).all())
+
+
+# block rows 1152 and 2601 of shapes the persistent kernel does not take: K = 64 mod 128 (the second
+# with 192-row tiles for Q|K|V and a gate/up product in two launches), one 128-wide and two 64-wide
+# KV heads
+@pytest.mark.parametrize("hidden,ffn,nq,nkv,hd,gamma,batch", [(192, 320, 4, 2, 128, 11, 8), (192, 3136, 14, 2, 128, 16, 9),
+                                                              (256, 384, 3, 1, 128, 11, 8), (256, 384, 4, 2, 64, 11, 8)])
+def test_backbone_above_1024_rows(hidden, ffn, nq, nkv, hd, gamma, batch):
+    from paper_2609_27396_amd.harness import DeviceRound
+    s = synth.DrafterShape(n_layers=1, hidden=hidden, n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, ffn=ffn, vocab=1000,
+                           gamma=gamma, ar_rank=64, qk_norm=True, dtype="bf16")
+    _say("case backbone above 1024", hidden, ffn, nq, nkv, hd)
+    ctx = [(61 * i + 5) % 190 for i in range(batch)]
+    wl = synth.Workload("above_1024", s, batch=batch, ctx_min=0, ctx_max=0, p_reject=0.3, seed_in=7)
+    w = synth.make_weights(s, seed=3, gain_jitter=0.1)
+    ri = synth.make_round(wl, ctx_lens=ctx)
+    dr = DeviceRound(s, w, ri)
+    dr.backbone()
+    assert dr.status() == 0
+    for b in (0, batch // 2, batch - 1):
+        ref = O.backbone_all_boundaries(s, w, ri.ctx_feats[b], ri.spine[b], "bf16")["reps"]
+        assert np.abs(dr.reps[b].cpu().numpy() - ref).max() <= TOL, b
+
+
+# candidates and the plain head where K is no multiple of 128; branch rows 252 (one 256-row tile), 360,
+# 1620 (256 x 256 tiles); head rows 36, 36, 162 (one 256-row tile of two planes)
+@pytest.mark.parametrize("batch,gamma", [(6, 6), (4, 9), (18, 9)])
+def test_candidates_with_hidden_192(batch, gamma):
+    candidates_are_the_plain_head(batch, gamma, 192)
