@@ -100,6 +100,15 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | (0x7 << 4) | (0xF << 8) | (((N >> 4) & 3) << 14));
 }
 
+// Between the stores of a wave's lanes to LDS and other lanes' reads of them, and before the next
+// stores there.  The LDS runs a wave's accesses in order; this keeps the compiler, which sees one
+// lane, from moving or dropping them.  No instruction.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Cross-lane moves inside 16-lane rows by DPP (no LDS round trip): quad_perm xor 1 and
 // xor 2, then the half-row and row mirrors.  After the four steps every lane of a row
 // holds the row's reduction.

@@ -306,6 +306,7 @@ __global__ __launch_bounds__(64 * WMW * WNW) void gemm_pipe_kernel(GemmArgs a, i
         for (int ni = 0; ni < FN; ++ni) stg[lrow * LDT + ni * 16 + lr] = f2bf(v[ni]);
       }
     }
+    wave_lds_fence();
     if (!isv) {
       // row pieces: lane (rq, piece) stores 16 bytes = columns 8 piece .. +7 of rows rq, rq+4, ...
       const int piece = lane & 15;

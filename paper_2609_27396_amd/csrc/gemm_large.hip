@@ -165,9 +165,11 @@ __device__ __forceinline__ void head_transposed(const f32x4_t (&acc)[WM / 16][8]
     for (int mi = 0; mi < WM / 16; ++mi)
 #pragma unroll
       for (int r = 0; r < 4; ++r) stg[(lc * 4 + r) * 64 + mi * 16 + lr] = f2bf(acc[mi][ni][r]);
+    wave_lds_fence();
     if (on)
 #pragma unroll 8
       for (int d = 0; d < 16; ++d) dst[(int64_t)(ni * 16 + d) * stride] = stg[d * 64 + lane];
+    wave_lds_fence();
   }
 }
 
