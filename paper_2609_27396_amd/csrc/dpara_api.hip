@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <string>
@@ -128,7 +129,8 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
   p.B = B;
   p.R = R > 0 ? R : (c->gamma + 1) * (c->gamma + 1);
   p.Rp = (p.R + 63) / 64 * 64;
-  p.M = B * p.R;
+  const size_t M = (size_t)B * p.R;
+  p.M = (int)std::min<size_t>(M, INT32_MAX);  // (more rows than any device holds: a size only)
   p.esz = c->dtype == DPARA_BF16 ? 2 : 4;
   const int hd = c->head_dim, nq = c->n_q_heads, nkv = c->n_kv_heads, H = c->hidden;
   const int grp = nq / nkv;
@@ -140,9 +142,9 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
     // batch 1 (targets 384 / 512 / 768: 44.9 / 43.2 / 50.7 us per layer with the fold, 41.8 at
     // 256).
     const int tiles = (grp * p.R + attn_rows_per_workgroup() - 1) / attn_rows_per_workgroup();
-    const int base = B * nkv * tiles;
+    const int64_t base = (int64_t)B * nkv * tiles;
     const int max_blocks = (ctx_cap + 63) / 64 + p.Rp / 64;
-    int S = DPARA_ATTN_TARGET_WG / base;
+    int S = (int)(DPARA_ATTN_TARGET_WG / base);
     const int max_s = min(max_blocks / 2, kMaxAttnSplits);
     if (S > max_s) S = max_s;
     if (S < 1) S = 1;
@@ -158,7 +160,7 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
       // 665 -> 609 us per layer with the fold); with more rounds, or contexts of mixed lengths,
       // the fold costs more than it saves (Qwen3-8B batch 16: 447 -> 479 us).
       constexpr int kSlots = 512;
-      const int rounds = (base + kSlots - 1) / kSlots;
+      const int64_t rounds = (base + kSlots - 1) / kSlots;
       if (rounds <= 2 && base % kSlots != 0 && base % kSlots <= kSlots * 7 / 10) S = 2;
     }
     p.S = S;
@@ -184,7 +186,6 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
   p.s_qkv = p.qkv_fused ? 1 : gemm_splits(p.afrag ? A_BF16_FRAG : amode, EPI_STORE_F32, p.M, (nq + 2 * nkv) * hd, H, kv_seg);
   p.s_o = gemm_splits(amode, EPI_STORE_F32, p.M, H, nq * hd);
   p.s_down = gemm_splits(amode, EPI_STORE_F32, p.M, H, c->ffn);
-  const size_t M = p.M;
   size_t off = 256;  // status header
   auto take = [&](size_t bytes) {
     size_t o = off;
@@ -235,11 +236,18 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
 }
 
 // Bytes for up to B requests: the key splits and the split-K planes fall with the rows, so a smaller
-// batch's plan can be the larger one (16 requests of gamma 4: 414 MB, 18: 410).
+// batch's plan can be the larger one (16 requests of gamma 4: 414 MB, 18: 410).  Every batch's plan
+// is looked at up to kPlans (50 ms); for more requests attention no longer splits, and the planes
+// of a bf16 model are taken as eight, the most above 320 rows.
 size_t plan_bytes(const dpara_config_t* c, int B, int ctx_cap, int R) {
+  constexpr int kPlans = 1 << 16;
   size_t n = 0;
-  for (int b = 1; b <= B; ++b) n = std::max(n, make_plan(c, b, ctx_cap, R).total);
-  return n;
+  for (int b = 1; b <= std::min(B, kPlans); ++b) n = std::max(n, make_plan(c, b, ctx_cap, R).total);
+  if (B <= kPlans) return n;
+  const Plan p = make_plan(c, B, ctx_cap, R);
+  if (c->dtype != DPARA_BF16) return std::max(n, p.total);
+  const size_t cols = (size_t)(c->n_q_heads + 2 * c->n_kv_heads) * c->head_dim + c->hidden;
+  return std::max(n, p.total + 8 * (size_t)B * p.R * cols * 4);
 }
 
 std::mutex g_dev_mu;

@@ -5,6 +5,7 @@ import ctypes
 import dataclasses
 import os
 import re
+import time
 
 import pytest
 
@@ -36,6 +37,16 @@ def test_workspace_serves_smaller_batches(gamma, size):
     for cap in (64, 2048, 8192):
         n = [size(cfg, b, cap) for b in range(1, 21)]
         assert n == sorted(n), cap
+
+
+def test_workspace_of_any_batch():
+    """Sizes grow with the batch, and a batch no device could hold is answered at once."""
+    for shape in (synth.QWEN3_8B, synth.TINY, synth.shrink(synth.QWEN3_8B, hidden=64, ffn=65536, head_dim=64, gamma=1)):
+        cfg = D.make_config(shape)
+        t = time.monotonic()
+        n = [D.dpara_workspace_bytes(cfg, b, 2048) for b in (1 << 10, 1 << 16, (1 << 16) + 1, 1 << 28, 2 ** 31 - 1)]
+        assert time.monotonic() - t < 20
+        assert 0 < n[0] and n == sorted(n)
 
 
 def test_workspace_bytes():
