@@ -17,7 +17,7 @@
 // 16-byte LDS read.  P enters the PV product as a bf16 hi + lo pair (two MFMAs), so the
 // probabilities keep ~16 significant bits: a single bf16 rounding of P moves the result
 // by about one bf16 ulp of the hidden state, which is as large as the whole error budget.
-// With one workgroup per row tile (S == 1) the kernel normalises and writes O itself;
+// With one workgroup per row tile (one split) the kernel normalises and writes O itself;
 // otherwise each writes an unnormalised partial (O, m, l) and attn_fold combines them.
 #include <math.h>
 
@@ -120,18 +120,28 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma(AttnArgs a) {
   // are the slowest index, so an XCD's range holds the same heads of every request (with 8 KV
   // heads, one head each) and the XCDs get equal shares of a batch of mixed context lengths;
   // within it the requests come longest context first, so the short ones fill the last round.
+  // The requests with a.split_len keys or more, the first n_split, have S splits, the others one:
+  // the workgroups left over are the last and return at once (dealt between the others they kept
+  // those off idle CUs: a layer of 3 requests of 1000 keys 454 us, so 435).
   const int n_tiles = (grp_rows(a) + ROWS_WG - 1) / ROWS_WG;
-  const int total = n_tiles * a.S * a.B * a.n_kv;
+  const bool ranked = a.B > 1 && a.B <= 64;
+  // lane t: the context length of request t (no barrier: every wave the same)
+  const int t = threadIdx.x & 63;
+  const int Lt = t < (ranked ? a.B : 1) ? min(max(a.ctx_len[t], 0), a.cap) : -1;
+  const int n_split = a.split_len > 0 ? __popcll(__ballot(Lt >= a.split_len)) : a.B;
+  const int per_kvh = (n_split * (a.S - 1) + a.B) * n_tiles, total = per_kvh * a.n_kv;
   const int p = blockIdx.x, per_xcd = total >> 3;
+  if (p >= total) return;
   const int lid = p < (per_xcd << 3) ? (p & 7) * per_xcd + (p >> 3) : p;
-  const int tile = lid % n_tiles, split = (lid / n_tiles) % a.S, hb = lid / (n_tiles * a.S);
-  const int kvh = hb / a.B, rank = hb % a.B;
+  const int tile = lid % n_tiles, kvh = lid / per_kvh;
+  const int unit = lid / n_tiles - kvh * (per_kvh / n_tiles), n_part = n_split * a.S;
+  const int S = unit < n_part ? a.S : 1;
+  const int split = unit < n_part ? unit % a.S : 0;
+  const int rank = unit < n_part ? unit / a.S : unit - n_part + n_split;
   int b = rank;
-  if (a.B > 1 && a.B <= 64) {
+  if (ranked) {
     // the request of this rank by (context length descending, index ascending): lane t ranks
-    // request t, every wave the same (no barrier), and the ballot picks the one lane
-    const int t = threadIdx.x & 63;
-    const int Lt = t < a.B ? min(max(a.ctx_len[t], 0), a.cap) : -1;
+    // request t and the ballot picks the one lane
     int r = 0;
     for (int u = 0; u < a.B; ++u) {
       const int Lu = min(max(a.ctx_len[u], 0), a.cap);
@@ -144,7 +154,7 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma(AttnArgs a) {
   const int L = min(max(a.ctx_len[b], 0), a.cap);
   const int nb_ctx = (L + kKeyBlock - 1) / kKeyBlock;
   const int nb = nb_ctx + (a.R + kKeyBlock - 1) / kKeyBlock;
-  const int per = (nb + a.S - 1) / a.S;
+  const int per = (nb + S - 1) / S;
   const int vb_begin = min(nb, split * per);
   const int n_blk = min(nb, vb_begin + per) - vb_begin;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -383,7 +393,7 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma(AttnArgs a) {
     if (qi[u] >= nrows) continue;
     const int gi = qi[u] / a.R, row = qi[u] % a.R;
     const int h = kvh * grp + gi;
-    if (a.S == 1) {
+    if (S == 1) {
       const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
       bf16_t* op = (bf16_t*)a.O + (int64_t)(b * a.R + row) * (a.n_q * HD) + h * HD;
 #pragma unroll
@@ -408,7 +418,7 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma(AttnArgs a) {
   }
 }
 
-// Folds the S partials of one (request, head, row): 4 head_dim entries per thread.
+// Folds the S partials of one (head, row) of request blockIdx.y: 4 head_dim entries per thread.
 // Partials with l == 0 saw no key and are skipped (their O was not written): every
 // partial is loaded up front, so the loads overlap, and an unwritten one is replaced by
 // zero with a select (never multiplied), so that stale memory cannot reach the result.
@@ -416,13 +426,12 @@ template <int HD>
 __global__ __launch_bounds__(256) void attn_fold(AttnArgs a) {
   constexpr int TPR = HD / 4;  // threads per (request, head, row)
   constexpr int SMAX = kMaxAttnSplits;
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t task = t / TPR;
-  if (task >= (int64_t)a.B * a.n_q * a.R) return;
-  const int c = (int)(t % TPR);
-  const int row = (int)(task % a.R);
-  const int bh = (int)(task / a.R), h = bh % a.n_q, b = bh / a.n_q;
-  const int64_t pbase = task * a.S;
+  const int b = blockIdx.y;
+  if (min(max(a.ctx_len[b], 0), a.cap) < a.split_len) return;  // one split: attn_mfma wrote O
+  const int t = blockIdx.x * 256 + threadIdx.x, hr = t / TPR, c = t % TPR;
+  if (hr >= a.n_q * a.R) return;
+  const int h = hr / a.R, row = hr - h * a.R;
+  const int64_t pbase = ((int64_t)b * a.n_q * a.R + hr) * a.S;
   float2 ml[SMAX];
   float4 v[SMAX];
 #pragma unroll
@@ -583,8 +592,8 @@ hipError_t run_attention_bf16(const AttnArgs& a, hipStream_t st) {
   if (e != hipSuccess || a.S == 1) return e;
   {
     Phase ph("attn_merge", st);
-    const int64_t threads = (int64_t)a.B * a.n_q * a.R * (HD / 4);
-    hipLaunchKernelGGL((attn_fold<HD>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a);
+    const int threads = a.n_q * a.R * (HD / 4);
+    hipLaunchKernelGGL((attn_fold<HD>), dim3((threads + 255) / 256, a.B), dim3(256), 0, st, a);
   }
   return hipGetLastError();
 }
@@ -611,7 +620,9 @@ hipError_t run_attention_scalar(const AttnArgs& a, hipStream_t st) {
 int attn_rows_per_workgroup() { return kRowsPerWG; }
 
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t st) {
-  if (a.Rp < a.R || a.Rp % kKeyBlock || a.S < 1 || a.S > kMaxAttnSplits) return hipErrorInvalidValue;
+  if (a.Rp < a.R || a.Rp % kKeyBlock || a.S < 1 || a.S > kMaxAttnSplits ||
+      (a.split_len > 0 && a.B > 64))
+    return hipErrorInvalidValue;
   if (dtype == 1) return a.hd == 128 ? run_attention_bf16<128>(a, st) : run_attention_bf16<64>(a, st);
   if (a.S != 1) return hipErrorInvalidValue;
   return a.hd == 128 ? run_attention_scalar<float, 128>(a, st) : run_attention_scalar<float, 64>(a, st);

@@ -17,6 +17,10 @@
 #define DPARA_ATTN_TARGET_WG 256
 #endif
 
+#ifndef DPARA_ATTN_SPLIT_LEN
+#define DPARA_ATTN_SPLIT_LEN 1024
+#endif
+
 using namespace dpara;
 
 namespace {
@@ -114,6 +118,7 @@ int check_ctx(const dpara_ctx_t* x, int batch) {
 // Workspace layout (byte offsets), shared by all calls.
 struct Plan {
   int B, R, Rp, M, S, chunk, CH, esz;
+  int split_len;           // attention: requests with fewer cached keys take one split
   int s_qkv, s_o, s_down;  // split-K planes of the QKV, O and down projections
   bool afrag;              // the attention norm's output in MFMA fragment order (QKV GEMM)
   bool qkv_fused;          // the QKV GEMM applies q/k-norm and RoPE in its epilogue
@@ -149,10 +154,15 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
     if (S > max_s) S = max_s;
     if (S < 1) S = 1;
     // Between half and all of the CUs: a split of two lets the short halves of mixed contexts fill
-    // in behind the long ones (a layer of 3 requests, contexts 700-3000: 480 -> 473 us; 911-4084:
-    // 481 -> 445; equal contexts of 2752: 548 -> 541).  Not for short contexts (144 and 555 keys:
-    // 382 -> 386, 383 -> 389) and not at one workgroup per CU (2322 keys: 507 -> 509).
-    if (base > DPARA_ATTN_TARGET_WG / 2 && base < DPARA_ATTN_TARGET_WG && ctx_cap >= 2048) S = 2;
+    // in behind the long ones (a layer of 3 requests, contexts 911-4084: 493 -> 474 us, 200-8000:
+    // 584 -> 534; of 2, 500-4000: 451 -> 412).  Short contexts lose by it (3 of 144 keys 402 -> 416,
+    // 9 of 300 at gamma 8 371 -> 382), so the kernel splits each request by its own length,
+    // whatever the cache holds (these 405 and 373; lengths of 1000 to 2100 keys are even either way).
+    // Not at one workgroup per CU (2322 keys: 507 -> 509).
+    if (base > DPARA_ATTN_TARGET_WG / 2 && base < DPARA_ATTN_TARGET_WG && B <= 64 && ctx_cap >= DPARA_ATTN_SPLIT_LEN) {
+      S = 2;
+      p.split_len = DPARA_ATTN_SPLIT_LEN;
+    }
     if (base > DPARA_ATTN_TARGET_WG && max_s >= 2) {
       // Large batches: two workgroups fit on a CU (512 at once).  When the workgroups make at
       // most two rounds and the last one is at most 70% full, a split of two fills the rounds
@@ -413,6 +423,7 @@ int run_decoder(const dpara_config_t* cfg, const dpara_layer_weights_t* layers, 
     aa.cap = ctx->ctx_cap;
     aa.ctx_len = ctx->ctx_len;
     aa.S = p.S;
+    aa.split_len = p.split_len;
     aa.chunk = p.chunk;
     aa.Opart = at<float>(ws, p.Opart);
     aa.MLpart = at<float>(ws, p.ML);

@@ -136,6 +136,7 @@ struct AttnArgs {
   int cap;
   const int* ctx_len;  // [B] device
   int S, chunk;        // bf16: keys split over S workgroups; float32: S == 1, chunk == cap
+  int split_len;       // bf16: requests with fewer cached keys take one split (> 0: B <= 64)
   float* Opart;        // [B, n_q, R, S, hd]
   float* MLpart;       // [B, n_q, R, S, 2]  (running max in log2 units, running sum)
   void* O;             // [B*R, n_q*hd]
