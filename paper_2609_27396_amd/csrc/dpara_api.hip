@@ -601,11 +601,22 @@ int dpara_ctx_append(const dpara_config_t* cfg, const dpara_weights_t* w, const 
   const size_t esz = p.esz;
   // More than 320 feature rows of a bf16 drafter with 128-wide heads: the projection reads the
   // features where they are and its epilogue writes the caches, over all rows of up to
-  // kMaxKvRows at a time; the RoPE table of those rows takes the fp32 planes' region.  Fewer rows
-  // fill the chip only with K split over workgroups, whose planes kv_store adds up.
+  // kMaxKvRows at a time; the RoPE table of those rows takes the fp32 planes' region.  Fewer rows or
+  // columns fill the chip only with K split over workgroups, whose planes kv_store adds up.
   const int64_t rows = (int64_t)batch * n_max;
-  if (dt == DPARA_BF16 && hd == 128 && rows > 320 && rows <= INT32_MAX / 2 && H % 128 == 0 && H >= 256 &&
-      nkv % 2 == 0) {
+  const bool epi = dt == DPARA_BF16 && hd == 128 && rows > 320 && rows <= INT32_MAX / 2 && H % 128 == 0 && H >= 256 &&
+                   nkv % 2 == 0;
+  // The epilogue's time is one tile's K loop however few the tiles are; the planes' grows with rows
+  // and columns (and takes the RoPE table at its region's end) and holds a store pass.  They meet
+  // near rows x columns = 800 (K - 300), from K 6000 on near 4.7 million (72 tiles of 256 x 256): at K
+  // 1024, 330 rows of one layer (2048 columns) take 31 us by the epilogue and 33 by planes; at 2048,
+  // 600 rows 42 and 36, 1200 44 and 50; at 4096 (two layers) 400 rows 64 and 49, 900 68 and 68, 1200
+  // 72 and 84; at 8192 (three) 600 rows 111 and 104, 900 124 and 130.
+  const int64_t cols = (int64_t)std::min(cfg->n_layers, kMaxAppendLayers) * 2 * nkv * hd;
+  const size_t tab_bytes = up256((size_t)rows * (hd / 2) * 8);
+  const bool planes = epi && rows * cols <= std::min<int64_t>(800 * (int64_t)(H - 300), 72 * 65536) &&
+                      (size_t)(rows * cols) * 4 + tab_bytes <= p.rope_app - p.KV32;
+  if (epi && !planes) {
     const int64_t fit = (int64_t)(p.rope_app - p.KV32) / (64 * 8);
     const int most = fit < kMaxKvRows ? (int)fit : kMaxKvRows;
     const int chunks = (int)((rows + most - 1) / most), CR = (int)((rows + chunks - 1) / chunks);
@@ -645,16 +656,18 @@ int dpara_ctx_append(const dpara_config_t* cfg, const dpara_weights_t* w, const 
     HIP_TRY(launch_ctx_len_update(batch, n_max, ctx->ctx_cap, n_new, ctx->ctx_len, status, st), "ctx_len_update");
     return DPARA_OK;
   }
-  const int CH = n_max < p.CH ? n_max : p.CH;  // rows per request per chunk
+  const int CH = planes || n_max < p.CH ? n_max : p.CH;  // rows per request per chunk
   // One chunk: the features are the GEMM's operand as they are, and the last store updates the
   // lengths (the stores then read the first positions that the table's launch kept), so a round's
   // update is a copy and a launch less: Qwen3-8B, batch 1, 59 -> 55 us.
   const bool whole = CH == n_max;
   int* pos0 = whole ? at<int>(ws, p.F) : nullptr;
+  const size_t tab = planes ? p.rope_app - tab_bytes : p.rope_app;
+  float2* table = at<float2>(ws, tab);
   for (int c0 = 0; c0 < n_max; c0 += CH) {
     if (!whole)
       HIP_TRY(launch_gather_feats(dt, batch, CH, c0, n_max, H, feats, at<void>(ws, p.F), st), "gather_feats");
-    HIP_TRY(launch_rope_table(batch, CH, hd, cfg->rope_base, ctx->ctx_len, c0, at<float2>(ws, p.rope_app), st, pos0),
+    HIP_TRY(launch_rope_table(batch, CH, hd, cfg->rope_base, ctx->ctx_len, c0, table, st, pos0),
             "rope_table");
     // All layers project the same features: up to kMaxAppendLayers layers share one K|V GEMM
     // (weight segments W_k, W_v of each layer) and one store launch.
@@ -676,17 +689,15 @@ int dpara_ctx_append(const dpara_config_t* cfg, const dpara_weights_t* w, const 
       g.C = at<void>(ws, p.KV32);
       g.ldc = g.N;
       g.splits = gemm_splits(dt == DPARA_BF16 ? A_BF16 : A_F32, EPI_STORE_F32, g.M, g.N, g.K, g.seg_rows);
-      if (g.M > 320) {  // the planes fit the region of make_plan
-        const int kv_rows = batch * p.CH > 16 * 320 ? batch * p.CH : 16 * 320;
-        while (g.splits > 1 && g.splits * g.M > kv_rows) --g.splits;
-      }
+      if (g.M > 320)  // the planes fit the region of make_plan
+        while (g.splits > 1 && (size_t)g.splits * g.M * g.N * 4 > tab - p.KV32) --g.splits;
       {
         Phase ph("append_gemm", st);
         HIP_TRY(launch_gemm(dt == DPARA_BF16 ? A_BF16 : A_F32, EPI_STORE_F32, g, st), "append kv gemm");
       }
       Phase ph("append_store", st);
       HIP_TRY(launch_kv_store(dt, batch, CH, c0, n_max, nkv, hd, cfg->qk_norm, cfg->rms_eps,
-                              at<float2>(ws, p.rope_app), at<float>(ws, p.KV32), g.splits, nl, kn, n_new,
+                              table, at<float>(ws, p.KV32), g.splits, nl, kn, n_new,
                               whole ? pos0 : ctx->ctx_len, ctx->ctx_cap, (char*)ctx->k + l0 * layer_elems * esz,
                               (char*)ctx->v + l0 * layer_elems * esz, layer_elems,
                               whole && l0 + nl == cfg->n_layers ? ctx->ctx_len : nullptr, status, st),

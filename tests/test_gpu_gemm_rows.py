@@ -131,21 +131,11 @@ def test_candidate_rows_around_tile_edges(batch, gamma):
     candidates_are_the_plain_head(batch, gamma, 256)
 
 
-# rows of one append: just above 320, row tiles of padding only, two layer groups, an append past the
-# cache's end, and more rows than one launch takes
-@pytest.mark.parametrize("layers,starts,counts,n_max,cap,step", [
-    (2, [0, 3, 0], [107, 1, 106], 107, 128, 53),
-    (9, [5, 0, 70, 9], [700, 0, 133, -2], 700, 640, 70),
-    (1, [1, 64], [9000, 4097], 9000, 9088, 160),
-])
-def test_prompt_append_is_its_short_appends(layers, starts, counts, n_max, cap, step):
-    """A prompt's rows appended at once (one projection that writes the caches) against the same
-    rows in appends of at most 320 rows (projection, then a store pass): lengths equal, entries
-    nobody appended untouched, the others within one bf16 rounding (float32 sums in another order)."""
+def append_is_its_short_appends(layers, starts, counts, n_max, cap, step, hidden):
     from paper_2609_27396_amd import dpara as D
     B = len(starts)
     assert B * n_max > 320 and B * step <= 320
-    s = synth.DrafterShape(n_layers=layers, hidden=384, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn=256, vocab=500,
+    s = synth.DrafterShape(n_layers=layers, hidden=hidden, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn=256, vocab=500,
                            gamma=4, ar_rank=64, qk_norm=True, dtype="bf16")
     _say("case prompt append", layers, B, n_max)
     dd = D.DeviceDrafter(s, synth.make_weights(s, seed=31, gain_jitter=0.1))
@@ -174,6 +164,30 @@ def test_prompt_append_is_its_short_appends(layers, starts, counts, n_max, cap, 
         assert torch.equal(a == mark, b == mark)
         a, b = a.float(), b.float()
         assert bool(((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5).all())
+
+
+# rows of one append: just above 320, row tiles of padding only, two layer groups, an append past the
+# cache's end, and more rows than one launch takes
+@pytest.mark.parametrize("layers,starts,counts,n_max,cap,step", [
+    (2, [0, 3, 0], [107, 1, 106], 107, 128, 53),
+    (9, [5, 0, 70, 9], [700, 0, 133, -2], 700, 640, 70),
+    (1, [1, 64], [9000, 4097], 9000, 9088, 160),
+])
+def test_prompt_append_is_its_short_appends(layers, starts, counts, n_max, cap, step):
+    """A prompt's rows appended at once (one projection that writes the caches) against the same
+    rows in appends of at most 320 rows (projection, then a store pass): lengths equal, entries
+    nobody appended untouched, the others within one bf16 rounding (float32 sums in another order)."""
+    append_is_its_short_appends(layers, starts, counts, n_max, cap, step, 384)
+
+
+# more than 320 rows, rows x columns at most 800 (K - 300): K split into planes, over all rows at once; an append past the cache's end, and two layer groups
+@pytest.mark.parametrize("layers,starts,counts,n_max,cap,step,hidden", [
+    (1, [0, 3, 0], [200, 1, 190], 200, 256, 100, 1024),
+    (2, [5, 0, 70], [190, 0, 188], 190, 256, 53, 1024),
+    (9, [0, 3], [250, -2], 250, 256, 125, 4096),
+])
+def test_append_of_few_columns_is_its_short_appends(layers, starts, counts, n_max, cap, step, hidden):
+    append_is_its_short_appends(layers, starts, counts, n_max, cap, step, hidden)
 
 
 # batch * gamma rows: 15, 64 | 66, 128 | 135, 192 | 198, 256 | 260, 320
