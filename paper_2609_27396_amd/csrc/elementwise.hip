@@ -262,17 +262,17 @@ __device__ __forceinline__ int appended_len(int L, int raw, int n_max, int cap, 
 }
 
 // K/V of appended rows: k = RoPE(kNorm(W_k f)) at its position, v = W_v f; K rows go to
-// [pos][hd], V to the transposed cache [hd][pos].  ctx_len: the lengths before the append; len_out
-// (NULL: another launch does it) gets those after it.
+// [pos][hd], V to the transposed cache [hd][pos].  ctx_len: the lengths before the append; LEN: len_out
+// gets those after it (a test at run time made every store 5% longer).
 // Grid (kv-head groups of 4, rows, layers).
-template <typename T>
+template <typename T, bool LEN>
 __global__ __launch_bounds__(256) void kv_store(int CH, int c0, int n_max, int n_kv, int hd, int qk_norm, float eps,
                                                 const float2* rope, const float* KV, int S, int64_t pstride,
                                                 KvLayers kls, const int* n_new, const int* ctx_len, int cap,
                                                 T* Kc, T* Vc, int64_t layer_elems, int* len_out, int* status) {
   const int m = blockIdx.y, b = m / CH, i = m % CH, l = blockIdx.z, nl = gridDim.z;
   const int c = c0 + i;
-  if (len_out && i == 0 && l == 0 && blockIdx.x == 0 && threadIdx.x == 0)
+  if (LEN && i == 0 && l == 0 && blockIdx.x == 0 && threadIdx.x == 0)
     len_out[b] = appended_len(max(ctx_len[b], 0), n_new[b], n_max, cap, status);
   if (c >= clamp_count(n_new[b], n_max)) return;
   const int pos = max(ctx_len[b], 0) + c;
@@ -487,15 +487,14 @@ hipError_t launch_kv_store(int dtype, int B, int CH, int c0, int n_max, int n_kv
   if (S < 1 || S > kMaxPlanes || nl < 1 || nl > kMaxAppendLayers) return hipErrorInvalidValue;
   const int64_t pstride = (int64_t)B * CH * nl * 2 * n_kv * hd;
   const dim3 grid((n_kv + 3) / 4, B * CH, nl);
-  if (dtype == 1)
-    hipLaunchKernelGGL(kv_store<bf16_t>, grid, dim3(256), 0, st, CH, c0, n_max, n_kv, hd, qk_norm, eps,
-                       rope, KV, S, pstride, kn, n_new, ctx_len, cap, (bf16_t*)Kc, (bf16_t*)Vc,
-                       (int64_t)layer_elems, len_out, status);
-  else
-    hipLaunchKernelGGL(kv_store<float>, grid, dim3(256), 0, st, CH, c0, n_max, n_kv, hd, qk_norm, eps,
-                       rope, KV, S, pstride, kn, n_new, ctx_len, cap, (float*)Kc, (float*)Vc,
-                       (int64_t)layer_elems, len_out, status);
-  return hipGetLastError();
+  auto go = [&](auto kern, auto* tag) {
+    using T = std::remove_pointer_t<decltype(tag)>;
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, CH, c0, n_max, n_kv, hd, qk_norm, eps, rope, KV, S, pstride, kn,
+                       n_new, ctx_len, cap, (T*)Kc, (T*)Vc, (int64_t)layer_elems, len_out, status);
+    return hipGetLastError();
+  };
+  if (dtype == 1) return len_out ? go(kv_store<bf16_t, true>, (bf16_t*)nullptr) : go(kv_store<bf16_t, false>, (bf16_t*)nullptr);
+  return len_out ? go(kv_store<float, true>, (float*)nullptr) : go(kv_store<float, false>, (float*)nullptr);
 }
 
 hipError_t launch_emit_hidden(int rows, int H, const float* X, const float* P, int S, int64_t pstride, void* out,
