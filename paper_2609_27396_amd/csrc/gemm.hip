@@ -670,10 +670,11 @@ hipError_t run_tall(const GemmArgs& a, hipStream_t st) {
   if constexpr (EPI == EPI_STORE_F32) {
     // Fewer than 192 tiles of 256 x 256 (under three quarters of one round, e.g. the
     // 2048-row feature fusion, 4096 columns: 128 tiles): 128 x 128 tiles at two workgroups
-    // per CU fill the chip instead, or 64 x 128 tiles where those give less than half of the CUs a
-    // workgroup (1156 rows x 1280 columns, the context append of one KV head: 139 -> 116 us for five layers).
+    // per CU fill the chip instead, or 64 x 128 tiles where those are at most 192 (1156 rows x 1280
+    // columns, the context append of one KV head: 139 -> 116 us for five layers; 190 tiles 154 -> 141, 280
+    // tiles 176 against 218).
     if (a.splits == 1 && (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256) < 192)
-      return (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) <= 128 ? run_pipe<64, 128, 2, 2, 3, 128, EPI>(a, st)
+      return (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) <= 192 ? run_pipe<64, 128, 2, 2, 3, 128, EPI>(a, st)
                                                                    : run_pipe<128, 128, 2, 2, 2, 128, EPI>(a, st);
     // One weight matrix, no split-K: when the last round of BM x 256 tiles is at most 60%
     // full, the columns of that round go to a second launch of 128 x 128 tiles (two
