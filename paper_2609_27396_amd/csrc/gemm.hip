@@ -813,9 +813,11 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st) {
   if (amode == A_BF16 && gemm_large_supported(epi, a)) return launch_gemm_large(epi, a, st);
   if (epi == EPI_TOP2) {  // at most 64 rows, or a K that is no multiple of 128
     if (amode != A_BF16) return hipErrorInvalidValue;
-    // 193-256 rows in one row tile, and 256 x 256 tiles from 1537 rows on (hidden 2880, 2176 rows:
-    // candidates 2626 -> 2488 us); else 192 x 128 tiles
-    if ((a.M > 192 && a.M <= 256) || a.M > 1536) return run_pipe<256, 256, 2, 4, 2, 128, EPI_TOP2, 0>(a, st);
+    // 193-256 rows in one row tile, and 256 x 256 tiles from 1537 rows on where they pad no more rows
+    // than 192 x 128 tiles (hidden 2880, 2176 rows, 2304 by either: candidates 2540 -> 2484 us; 1904
+    // rows, 2048 against 1920: 2117 -> 2240); else 192 x 128 tiles
+    const bool tall = a.M > 1536 && (a.M + 255) / 256 * 256 <= (a.M + 191) / 192 * 192;
+    if ((a.M > 192 && a.M <= 256) || tall) return run_pipe<256, 256, 2, 4, 2, 128, EPI_TOP2, 0>(a, st);
     return run_pipe<192, 128, 2, 2, 2, 128, EPI_TOP2, 0>(a, st);
   }
   if (epi == EPI_QKV) {  // the same shapes as run_tall, its row tiles
