@@ -187,13 +187,13 @@ Plan make_plan(const dpara_config_t* c, int B, int ctx_cap, int R = 0) {
   const int amode = c->dtype == DPARA_BF16 ? A_BF16 : A_F32;
   // From 193 to 320 rows the QKV GEMM reads its activations in fragment order.
   p.afrag = c->dtype == DPARA_BF16 && p.M > 192 && p.M <= 320 && H % 256 == 0;
-  // Above 320 rows the GEMM's epilogue applies q/k-norm and RoPE (128-wide heads): the persistent
-  // kernel where a 256-column tile lies within one of W_q, W_k, W_v, the LDS-pipeline kernel's tiles
-  // above 1024 rows otherwise; else split planes and the q/k-norm pass.
-  const int kv_seg = nkv * hd;  // divides n_q heads' columns too
-  p.qkv_fused = c->dtype == DPARA_BF16 && hd == 128 &&
-                (p.M > 1024 || (p.M > 320 && H % 128 == 0 && H >= 256 && kv_seg % 256 == 0));
-  p.s_qkv = p.qkv_fused ? 1 : gemm_splits(p.afrag ? A_BF16_FRAG : amode, EPI_STORE_F32, p.M, (nq + 2 * nkv) * hd, H, kv_seg);
+  // Above 320 rows the GEMM's epilogue can apply q/k-norm and RoPE (128-wide heads): the persistent
+  // kernel's, where a 256-column tile lies within one of W_q, W_k, W_v and that is the faster way,
+  // the LDS-pipeline kernel's above 1024 rows otherwise; else split planes and the q/k-norm pass.
+  const int kv_seg = nkv * hd, qkv_cols = (nq + 2 * nkv) * hd;  // kv_seg divides n_q heads' columns too
+  const bool large = p.M > 320 && H % 128 == 0 && H >= 256 && kv_seg % 256 == 0;
+  p.qkv_fused = c->dtype == DPARA_BF16 && hd == 128 && (large ? gemm_large_fuses_qkv(p.M, qkv_cols, H) : p.M > 1024);
+  p.s_qkv = p.qkv_fused ? 1 : gemm_splits(p.afrag ? A_BF16_FRAG : amode, EPI_STORE_F32, p.M, qkv_cols, H, kv_seg);
   p.s_o = gemm_splits(amode, EPI_STORE_F32, p.M, H, nq * hd);
   p.s_down = gemm_splits(amode, EPI_STORE_F32, p.M, H, c->ffn);
   size_t off = 256;  // status header

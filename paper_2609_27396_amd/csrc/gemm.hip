@@ -652,9 +652,10 @@ hipError_t run_pipe(const GemmArgs& a, hipStream_t st) {
 //             weight tile is read once; 8 waves (80x64 each), a 2-deep
 //             ring of 64-wide K steps.  The fp32-store GEMMs split K so that about 256 workgroups
 //             run; their consumers add the S partial planes (gemm_splits).
-//  above    : where a K that is no multiple of 128 or a weight segment that is no multiple of 256
-//             rows keeps the persistent kernel out: 64 x 128 tiles up to 1024 rows, above them
-//             256 x 256 (192 x 256 where these fill the rounds of the CUs better).
+//  above    : 64 x 128 tiles up to 1024 rows, for a short K (gemm_large_prefers_rows64) or where a K
+//             that is no multiple of 128 or a weight segment that is no multiple of 256 rows keeps
+//             the persistent kernel out; above 1024 rows, for the latter, 256 x 256 (192 x 256 where
+//             these fill the rounds of the CUs better).
 // Fraction of the last round of workgroups that has work (one workgroup per CU) for
 // BM x 256 tiles: 192-row tiles are taken when they fill the rounds clearly better.
 double round_fill(int M, int N, int BM) {
@@ -810,7 +811,8 @@ hipError_t launch_gemm(int amode, int epi, const GemmArgs& a, hipStream_t st) {
   if (epi == EPI_QKV && (amode != A_BF16 || a.splits != 1 || a.N != (a.qkv.n_q + 2 * a.qkv.n_kv) * 128 ||
                          a.qkv.n_kv < 1 || a.qkv.n_q % a.qkv.n_kv || a.qkv.R < 1 || a.qkv.Rp < a.qkv.R))
     return hipErrorInvalidValue;
-  if (amode == A_BF16 && gemm_large_supported(epi, a)) return launch_gemm_large(epi, a, st);
+  if (amode == A_BF16 && gemm_large_supported(epi, a) && !gemm_large_prefers_rows64(epi, a))
+    return launch_gemm_large(epi, a, st);
   if (epi == EPI_TOP2) {  // at most 64 rows, or a K that is no multiple of 128
     if (amode != A_BF16) return hipErrorInvalidValue;
     // 193-256 rows in one row tile, and 256 x 256 tiles from 1537 rows on where they pad no more rows

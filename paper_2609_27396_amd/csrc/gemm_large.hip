@@ -737,6 +737,34 @@ LargeTile large_choice(int M, int N, int K, int S, int cols_per_256, bool narrow
   return best;
 }
 
+// Estimated time, us, of the LDS-pipeline kernel's 64 x 128 tiles (gemm.hip) over NT column tiles: two
+// fit on a CU, so few rows of a short K, too few large tiles for the CUs, run them side by side.
+// A 64-deep K step takes 0.48 while a CU has one and up to 0.72 with two (fitted to 325 to 1024 rows,
+// K 1024 to 8192; only one round of the CUs).
+double rows64_time(int M, int NT, int K) {
+  if (M > 1024 || (M + 63) / 64 * NT > 2 * kCus) return 1e30;
+  const double T = M / 64.0 * NT;
+  return 0.5 + K / 64 * (T <= 256 ? 0.48 : T >= 352 ? 0.72 : 0.48 + 0.0025 * (T - 256));
+}
+
+// A float32 plane's store and its consumer's read (about 3.5 and 4 TB/s).
+double plane_time(int M, int N) { return (double)M * N * 4.0 * (1 / 3.5e6 + 1 / 4e6); }
+
+// Planes of the float32 store and their estimated time with the GEMM.  867 x 4096 x 12288: 195 us as
+// one plane, 84 as three.
+struct StoreChoice {
+  int S;
+  double us;
+};
+StoreChoice store_choice(int M, int N, int K) {
+  StoreChoice best{1, 1e30};
+  for (int S = 1; S <= 8 && K / 128 >= 2 * S; ++S) {
+    const double t = large_choice(M, N, K, S, 256, true).us + S * plane_time(M, N);
+    if (t < best.us) best = {S, t};
+  }
+  return best;
+}
+
 template <int BM, int BN, int EPI, int TAIL>
 hipError_t run_large_tail(const GemmArgs& a, const LargePlan& p, hipStream_t st) {
   constexpr int ring = (2 * BM + ring_depth(EPI, BM) * BN) * 128;
@@ -936,18 +964,26 @@ bool gemm_large_supported(int epi, const GemmArgs& a) {
 }
 
 int gemm_large_splits(int M, int N, int K) {
-  // Least estimated time: the GEMM and, for each plane, its store and the consumer's read (about
-  // 3.5 and 4 TB/s).  867 x 4096 x 12288: 195 us as one plane, 84 as three.
-  int best = 1;
-  double us = 1e30;
-  for (int S = 1; S <= 8 && K / 128 >= 2 * S; ++S) {
-    const double t = large_choice(M, N, K, S, 256, true).us + S * (double)M * N * 4.0 * (1 / 3.5e6 + 1 / 4e6);
-    if (t < us) {
-      us = t;
-      best = S;
-    }
-  }
-  return best;
+  const StoreChoice c = store_choice(M, N, K);
+  return rows64_time(M, (N + 127) / 128, K) + plane_time(M, N) < c.us ? 1 : c.S;
+}
+
+bool gemm_large_fuses_qkv(int M, int N, int K) {
+  // The fused epilogue has no split K: at few rows its tiles leave CUs idle, and the planes with the
+  // q/k-norm pass (about 11 us of its own) are faster, or one plane of 64-row tiles.  Qwen3-8B, 340 / 578
+  // / 867 / 1156 rows: fused 86 / 74 / 74 / 74 us, planes and pass 41 / 56 / 61 / 71 (64-row tiles 48 /
+  // 61 / 94); K 1024, 340 and 867 rows: 35 and 31, 33 and 46, 24 and 38.
+  const double us = large_choice(M, N, K, 1, 256, false).us;
+  return us <= store_choice(M, N, K).us + 1 && us <= rows64_time(M, (N + 127) / 128, K) + plane_time(M, N) + 3;
+}
+
+bool gemm_large_prefers_rows64(int epi, const GemmArgs& a) {
+  // gate/up 405 x 3072 x 1024 21 -> 13 us, Q|K|V 340 x 4096 x 2048 52 -> 31 with its pass
+  if (a.splits != 1) return false;
+  if (epi == EPI_SWIGLU)
+    return rows64_time(a.M, (a.N + 63) / 64, a.K) < large_choice(a.M, a.N, a.K, 1, 128, false).us;
+  return epi == EPI_STORE_F32 &&
+         rows64_time(a.M, (a.N + 127) / 128, a.K) < large_choice(a.M, a.N, a.K, 1, 256, true).us;
 }
 
 hipError_t launch_gemm_large(int epi, const GemmArgs& a, hipStream_t st) {

@@ -118,6 +118,10 @@ hipError_t launch_gemm_dual(const GemmArgs& a, hipStream_t st);
 bool gemm_large_supported(int epi, const GemmArgs& a);
 hipError_t launch_gemm_large(int epi, const GemmArgs& a, hipStream_t st);
 int gemm_large_splits(int M, int N, int K);  // split-K planes of its float32 store
+// Whether Q|K|V runs with its q/k-norm and RoPE epilogue there, and whether a call it takes is faster on
+// 64-row tiles of the LDS-pipeline kernel.
+bool gemm_large_fuses_qkv(int M, int N, int K);
+bool gemm_large_prefers_rows64(int epi, const GemmArgs& a);
 constexpr int kMaxKvRows = 64 * 256;         // rows of one EPI_KV launch
 // Split-K factor launch_gemm uses for a bf16 fp32-store GEMM of this shape (1 = no split).
 // The consumer of C sums the S planes in order 0..S-1.  seg: greatest common divisor of the

@@ -266,16 +266,20 @@ def test_fused_features_above_1024_rows(hidden, n):
 
 # block rows 1152 and 2601 of shapes the persistent kernel does not take: K = 64 mod 128 (the second
 # with 192-row tiles for Q|K|V and a gate/up product in two launches), one 128-wide and two 64-wide
-# KV heads
-@pytest.mark.parametrize("hidden,ffn,nq,nkv,hd,gamma,batch", [(192, 320, 4, 2, 128, 11, 8), (192, 3136, 14, 2, 128, 16, 9),
-                                                              (256, 384, 3, 1, 128, 11, 8), (256, 384, 4, 2, 64, 11, 8)])
-def test_backbone_above_1024_rows(hidden, ffn, nq, nkv, hd, gamma, batch):
+# KV heads; then of shapes it takes: its Q|K|V epilogue over 1152, 1183 and 2601 rows (last row tiles of
+# 128, 159 or 31 and 41 rows), and below that split-K planes of Q|K|V (338 rows, K 1024) and 64-row
+# tiles for Q|K|V and gate/up (338 and 1014 rows, K 256)
+@pytest.mark.parametrize("hidden,ffn,nq,nkv,hd,gamma,batch", [
+    (192, 320, 4, 2, 128, 11, 8), (192, 3136, 14, 2, 128, 16, 9), (256, 384, 3, 1, 128, 11, 8), (256, 384, 4, 2, 64, 11, 8),
+    (256, 384, 4, 2, 128, 11, 8), (384, 640, 4, 2, 128, 12, 7), (256, 384, 4, 2, 128, 16, 9),
+    (1024, 512, 4, 2, 128, 12, 2), (256, 384, 4, 2, 128, 12, 2), (256, 384, 4, 2, 128, 12, 6)])
+def test_backbone_rows(hidden, ffn, nq, nkv, hd, gamma, batch):
     from paper_2609_27396_amd.harness import DeviceRound
     s = synth.DrafterShape(n_layers=1, hidden=hidden, n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, ffn=ffn, vocab=1000,
                            gamma=gamma, ar_rank=64, qk_norm=True, dtype="bf16")
-    _say("case backbone above 1024", hidden, ffn, nq, nkv, hd)
+    _say("case backbone rows", hidden, ffn, nq, nkv, hd)
     ctx = [(61 * i + 5) % 190 for i in range(batch)]
-    wl = synth.Workload("above_1024", s, batch=batch, ctx_min=0, ctx_max=0, p_reject=0.3, seed_in=7)
+    wl = synth.Workload("rows", s, batch=batch, ctx_min=0, ctx_max=0, p_reject=0.3, seed_in=7)
     w = synth.make_weights(s, seed=3, gain_jitter=0.1)
     ri = synth.make_round(wl, ctx_lens=ctx)
     dr = DeviceRound(s, w, ri)
