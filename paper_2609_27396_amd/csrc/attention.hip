@@ -129,15 +129,17 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma(AttnArgs a) {
   const int t = threadIdx.x & 63;
   const int Lt = t < (ranked ? a.B : 1) ? min(max(a.ctx_len[t], 0), a.cap) : -1;
   const int n_split = a.split_len > 0 ? __popcll(__ballot(Lt >= a.split_len)) : a.B;
-  const int per_kvh = (n_split * (a.S - 1) + a.B) * n_tiles, total = per_kvh * a.n_kv;
+  const int per_kvh = n_split * (a.S - 1) + a.B, total = per_kvh * a.n_kv * n_tiles;
   const int p = blockIdx.x, per_xcd = total >> 3;
   if (p >= total) return;
   const int lid = p < (per_xcd << 3) ? (p & 7) * per_xcd + (p >> 3) : p;
-  const int tile = lid % n_tiles, kvh = lid / per_kvh;
-  const int unit = lid / n_tiles - kvh * (per_kvh / n_tiles), n_part = n_split * a.S;
-  const int S = unit < n_part ? a.S : 1;
-  const int split = unit < n_part ? unit % a.S : 0;
-  const int rank = unit < n_part ? unit / a.S : unit - n_part + n_split;
+  const int u0 = lid / n_tiles, tile = lid - u0 * n_tiles, kvh = u0 / per_kvh, unit = u0 - kvh * per_kvh;
+  int S = a.S, rank = unit / a.S, split = unit - rank * a.S;
+  if (rank >= n_split) {
+    rank = unit - n_split * (a.S - 1);
+    S = 1;
+    split = 0;
+  }
   int b = rank;
   if (ranked) {
     // the request of this rank by (context length descending, index ascending): lane t ranks
