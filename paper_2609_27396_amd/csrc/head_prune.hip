@@ -969,9 +969,11 @@ hipError_t launch_draft_scores(int dtype, int B, int gamma, int V, int rank, con
   g.C = cbuf;
   g.ldc = V;
   g.only_if = ok;  // (kernels that ignore it only waste work: the finishing pass checks ok)
-  // rank 256, up to 320 rows: the product's epilogue adds the logits and scales, so the products are
-  // neither stored nor read back (128 rows x 151936: 42 + 34 us in two launches)
-  if (dtype == 1 && gemm_score_supported(g)) {
+  // rank 256, 17 to 320 rows: the product's epilogue adds the logits and scales, so the products are
+  // neither stored nor read back (128 rows x 151936: 42 + 34 us in two launches).  Fewer rows are bound
+  // by W, which the tiles for few rows stream faster (sampled step of 8 and 16 rows, Qwen3-8B: 277 and
+  // 302 us, by the epilogue 282 and 304; 24 rows 321 either way).
+  if (dtype == 1 && R > 16 && gemm_score_supported(g)) {
     g.C = smp.scores;
     g.base = logits;
     g.scale = smp.inv_t;
