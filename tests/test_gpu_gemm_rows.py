@@ -295,3 +295,82 @@ def test_backbone_rows(hidden, ffn, nq, nkv, hd, gamma, batch):
 @pytest.mark.parametrize("batch,gamma", [(6, 6), (4, 9), (18, 9)])
 def test_candidates_with_hidden_192(batch, gamma):
     candidates_are_the_plain_head(batch, gamma, 192)
+
+
+# requests of 42 branch rows: one at a time they are ranked by the kernel for at most 64 rows, which
+# inserts a key for every logit; 84, 168, 252 | 294, 336 rows take the three largest values of a tile by
+# medians first
+@pytest.mark.parametrize("batch", [2, 4, 6, 7, 8])
+def test_candidates_with_ties_and_values_that_are_not_finite(batch):
+    """Equal leaders (two and three equal embedding rows in one full 128-column tile, equal rows in two
+    tiles, a tile and a row of zeros), infinities and NaN: every row's candidates and bound are bit for
+    bit those of its request alone."""
+    from paper_2609_27396_amd import dpara as D
+    gamma, V = 6, 3000
+    s = _shape(256, 256, V, gamma)
+    _say("case ties", batch)
+    w = synth.make_weights(s, seed=6, gain_jitter=0.1, ar_w_std=0.005, ar_e_std=0.02)
+    E = w["embed"]
+    E[700], E[703], E[701] = E[650], E[650], E[651]  # columns 640 .. 767: three, and two
+    E[131], E[1500] = E[130], E[130]                 # two in one tile, the third in another
+    E[2304:2432] = 0                                 # one whole tile
+    dd = D.DeviceDrafter(s, w)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(batch)
+    reps = torch.empty((batch, gamma + 1, gamma, s.hidden), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    Ed = torch.from_numpy(E).cuda()
+    flat = reps.view(batch, (gamma + 1) * gamma, s.hidden)
+    for b in range(batch):
+        for i, v in enumerate((650, 651, 130)):  # their logits lead
+            flat[b, (5 * b + i) % 42] += 300 * Ed[v]
+        flat[b, (5 * b + 7) % 42] = 0  # every logit 0
+        flat[b, (5 * b + 9) % 42, 3] = float("inf")
+        flat[b, (5 * b + 11) % 42, 5] = float("-inf")
+        flat[b, (5 * b + 13) % 42, 7] = float("nan")
+        flat[b, (5 * b + 15) % 42] = 3e38  # products that overflow
+    ref_rows = []
+    ws = D.Workspace(dd.cfg, batch, 64)
+
+    def rows_of(x):
+        cand = D.branch_candidates_buffer(dd, x.shape[0])
+        D.branch_candidates(dd, x, cand, ws)
+        torch.cuda.synchronize()
+        return cand[4096:].view(torch.int64).view(x.shape[0], 42, -1).cpu()
+
+    got = rows_of(reps)
+    for b in range(batch):
+        ref_rows.append(rows_of(reps[b:b + 1].contiguous())[0])
+    ref = torch.stack(ref_rows)
+    assert torch.equal(got, ref)
+    col = 0xFFFFFFFF - (got[:, :, :17] & 0xFFFFFFFF)
+    assert bool((col[:, :, :2] < V).all())
+    for b in range(batch):  # the lowest of equal columns leads
+        for i, lead in enumerate(((650, 700), (651, 701), (130, 131))):
+            assert tuple(col[b, (5 * b + i) % 42, :2].tolist()) == lead
+
+
+# 102, 170, 238 and 272 rows over more than 32768 columns (wide tiles), where four columns are one store and
+# where they are not
+@pytest.mark.parametrize("batch,vocab", [(6, 33000), (10, 33001), (14, 33000), (16, 33001)])
+def test_target_over_a_wide_vocabulary(batch, vocab):
+    from paper_2609_27396_amd import dpara as D
+    from paper_2609_27396_amd.harness import upload_cache
+    s = _shape(256, 256, vocab, 16)
+    lens = [(29 * i) % 70 for i in range(batch)]
+    _say("case target vocabulary", batch * 17, vocab)
+    w = synth.make_target_weights(s, seed=7, gain_jitter=0.1)
+    k, v = synth.make_target_cache(s, lens, seed=8)
+    block = np.random.default_rng(batch).integers(0, vocab, (batch, 17)).astype(np.int32)
+    t = D.DeviceTarget(s, w)
+    ctx = D.DeviceContext(s, batch, 128)
+    upload_cache(ctx, k, v, lens, torch.bfloat16)
+    ws = D.Workspace(t.cfg, batch, 128, target=True)
+    lf = torch.empty((batch, 17, vocab), dtype=torch.float32, device="cuda")
+    lb = torch.empty_like(lf, dtype=torch.bfloat16)
+    D.target_forward(t, ctx, torch.from_numpy(block).cuda(), lf, ws)
+    D.target_forward(t, ctx, torch.from_numpy(block).cuda(), lb, ws)
+    torch.cuda.synchronize()
+    for b in (0, batch - 1):
+        ref = O.target_forward(s, w, [k[0][b]], [v[0][b]], block[b], "bf16")
+        assert np.abs(lf[b].cpu().numpy() - ref).max() <= TOL, b
+    np.testing.assert_allclose(lb.float().cpu().numpy(), lf.cpu().numpy(), rtol=2 ** -8, atol=0)
