@@ -127,7 +127,8 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma(AttnArgs a) {
   const bool ranked = a.B > 1 && a.B <= 64;
   // lane t: the context length of request t (no barrier: every wave the same)
   const int t = threadIdx.x & 63;
-  const int Lt = t < (ranked ? a.B : 1) ? min(max(a.ctx_len[t], 0), a.cap) : -1;
+  int Lt = -1;
+  if ((ranked || a.split_len > 0) && t < a.B) Lt = min(max(a.ctx_len[t], 0), a.cap);
   const int n_split = a.split_len > 0 ? __popcll(__ballot(Lt >= a.split_len)) : a.B;
   const int per_kvh = n_split * (a.S - 1) + a.B, total = per_kvh * a.n_kv * n_tiles;
   const int p = blockIdx.x, per_xcd = total >> 3;
@@ -424,12 +425,13 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma(AttnArgs a) {
 // Partials with l == 0 saw no key and are skipped (their O was not written): every
 // partial is loaded up front, so the loads overlap, and an unwritten one is replaced by
 // zero with a select (never multiplied), so that stale memory cannot reach the result.
-template <int HD>
+// BY_LEN: where a.split_len > 0.
+template <int HD, bool BY_LEN>
 __global__ __launch_bounds__(256) void attn_fold(AttnArgs a) {
   constexpr int TPR = HD / 4;  // threads per (request, head, row)
   constexpr int SMAX = kMaxAttnSplits;
   const int b = blockIdx.y;
-  if (min(max(a.ctx_len[b], 0), a.cap) < a.split_len) return;  // one split: attn_mfma wrote O
+  if (BY_LEN && min(max(a.ctx_len[b], 0), a.cap) < a.split_len) return;  // one split: attn_mfma wrote O
   const int t = blockIdx.x * 256 + threadIdx.x, hr = t / TPR, c = t % TPR;
   if (hr >= a.n_q * a.R) return;
   const int h = hr / a.R, row = hr - h * a.R;
@@ -595,7 +597,8 @@ hipError_t run_attention_bf16(const AttnArgs& a, hipStream_t st) {
   {
     Phase ph("attn_merge", st);
     const int threads = a.n_q * a.R * (HD / 4);
-    hipLaunchKernelGGL((attn_fold<HD>), dim3((threads + 255) / 256, a.B), dim3(256), 0, st, a);
+    auto fold = a.split_len > 0 ? attn_fold<HD, true> : attn_fold<HD, false>;
+    hipLaunchKernelGGL(fold, dim3((threads + 255) / 256, a.B), dim3(256), 0, st, a);
   }
   return hipGetLastError();
 }
