@@ -838,8 +838,9 @@ hipError_t run_mid(const GemmArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Tiles for 65 to 320 rows, measured on MI355X at Qwen3-8B widths with the weights in HBM (us, and
-// what the kernels used before took):
+// Tiles for 65 to 320 rows, measured on MI355X at Qwen3-8B widths with the weights in HBM (us of one
+// product's launches back to back, and what the kernels used before took; between the other kernels of
+// a layer gate/up at 289 rows takes 69, and took 72):
 //  SwiGLU   : up to 128 rows 128 x 128 (192 workgroups at Qwen3-8B; 128 x 192 where that takes
 //             fewer rounds): 102 rows 46 (63), Qwen3-14B 73.  Above, two equal row tiles x 192
 //             columns by four waves, so that Qwen3-8B gives 256 workgroups and the two that share
